@@ -310,6 +310,9 @@ bool build_tables(int n, Tables<double>& T) {
       Cv[i * n + j] = cm;
       T.B[i * kMaxN + j] = B[i * n + j];
       T.D[i * kMaxN + j] = D[i * n + j];
+      T.BB[i * kMaxN + j] = B[i * n + j] * B[i * n + j];
+      T.BD[i * kMaxN + j] = B[i * n + j] * D[i * n + j];
+      T.DD[i * kMaxN + j] = D[i * n + j] * D[i * n + j];
     }
   for (int i = 0; i < n; ++i) {
     T.d0[i] = Dn[0 * n + i];
@@ -350,6 +353,9 @@ void tables_to_f32(const Tables<double>& a, Tables<float>& b) {
     b.B[i] = (float)a.B[i];
     b.D[i] = (float)a.D[i];
     b.Cd[i] = (float)a.Cd[i];
+    b.BB[i] = (float)a.BB[i];
+    b.BD[i] = (float)a.BD[i];
+    b.DD[i] = (float)a.DD[i];
   }
   for (int i = 0; i < kMaxN; ++i) {
     b.d0[i] = (float)a.d0[i];
@@ -552,10 +558,9 @@ hipError_t coef_setup(dg_ctx* c, const double* theta, int* changed, hipStream_t 
 // *run == 0 on the device (the coefficients did not change)
 hipError_t compute_dinv(dg_ctx* c, hipStream_t s, const int* run = nullptr) {
   const MeshArgs<double> m64 = args64(c);
-  hipError_t e = c->trilinear ? launch_diag_trilinear(c->n, m64, c->r64, run, s)
-                              : launch_diag_affine(c->n, m64, c->r64, run, s);
-  if (e != hipSuccess) return e;
-  e = launch_inv_diag(c->ndof, c->r64, c->dinv64, c->dinv32, run, s);
+  const DiagOut out{nullptr, c->dinv64, c->dinv32};
+  hipError_t e = c->trilinear ? launch_diag_trilinear(c->n, m64, out, run, s)
+                              : launch_diag_affine(c->n, m64, out, run, s);
   if (e != hipSuccess || c->trilinear) return e;
   // element block-Jacobi factors (cheap: one small eigenproblem per element and axis)
   return launch_bj_setup(c->n, m64, c->bjQ64, c->bjL64, c->bjQ32, c->bjL32, s);
@@ -850,8 +855,9 @@ int dg_diagonal(dg_ctx* c, double* d, void* stream) {
   if (!d) return fail(c, DG_ERR_ARG, "d is NULL");
   const MeshArgs<double> m64 = args64(c);
   hipStream_t s = (hipStream_t)stream;
-  HIP_TRY(c, c->trilinear ? launch_diag_trilinear(c->n, m64, d, nullptr, s)
-                          : launch_diag_affine(c->n, m64, d, nullptr, s));
+  const DiagOut out{d, nullptr, nullptr};
+  HIP_TRY(c, c->trilinear ? launch_diag_trilinear(c->n, m64, out, nullptr, s)
+                          : launch_diag_affine(c->n, m64, out, nullptr, s));
   return DG_OK;
 }
 

@@ -49,6 +49,9 @@ struct Tables {
                         // the element block-Jacobi preconditioner
   T Cd[kMaxN * kMaxN];  // mixed matrix C_ij = sum_q w_q l_i(x_q) l_j'(x_q) = int l_i l_j'
   EvenOdd<T> eC;        // C by its even-odd halves (centro-antisymmetric)
+  T BB[kMaxN * kMaxN];  // products of basis values and derivatives at the Gauss points,
+  T BD[kMaxN * kMaxN];  // B_qi B_qi, B_qi D_qi, D_qi D_qi: the diagonal a(phi_i, phi_i) by
+  T DD[kMaxN * kMaxN];  // sum factorisation (trilinear meshes)
 };
 
 // Eigen-decomposition of a symmetric n x n matrix (row stride kMaxN) by the

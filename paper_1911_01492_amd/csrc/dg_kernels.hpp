@@ -75,8 +75,23 @@ hipError_t launch_inner_start(int64_t n, const float* z, float* d, TP* p, const 
 hipError_t launch_init_inner_finish(const double* partials, int64_t nb, CgState* st, double rtol, hipStream_t s);
 hipError_t launch_face_coef(const MeshArgs<double>& m, double* G64, float* G32, hipStream_t s);
 hipError_t launch_finish_dot(const double* partials, int64_t nblocks, CgState* st, int par, hipStream_t s);
+// What a diagonal kernel writes: the diagonal, its inverse in FP64 and FP32
+// (each nullptr when not wanted).
+struct DiagOut {
+  double* d;
+  double* i64;
+  float* i32;
+  __device__ __forceinline__ void put(int64_t i, double v) const {
+    if (d) d[i] = v;
+    if (i64) {
+      const double w = 1.0 / v;
+      i64[i] = w;
+      i32[i] = (float)w;
+    }
+  }
+};
 // diagonal kernels: run != nullptr && *run == 0 makes them return at once
-hipError_t launch_diag_affine(int n, const MeshArgs<double>& m, double* d, const int* run, hipStream_t s);
+hipError_t launch_diag_affine(int n, const MeshArgs<double>& m, const DiagOut& out, const int* run, hipStream_t s);
 hipError_t launch_dA_affine(int n, const MeshArgs<double>& m, const double* u, const double* v, double* g,
                             hipStream_t s);
 
@@ -93,7 +108,7 @@ hipError_t launch_apply_ppd(int n, int prec, int dot, const MeshArgs<double>& m6
 // second grid dimension; no fused dot)
 hipError_t launch_apply_ppd_multi(int n, int prec, int nrhs, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
                                   const void* x, void* y, hipStream_t s);
-hipError_t launch_diag_trilinear(int n, const MeshArgs<double>& m, double* d, const int* run, hipStream_t s);
+hipError_t launch_diag_trilinear(int n, const MeshArgs<double>& m, const DiagOut& out, const int* run, hipStream_t s);
 // g_T = u^T dA/dtheta_T v on trilinear meshes; parts: 7 E doubles of scratch
 hipError_t launch_dA_trilinear(int n, const MeshArgs<double>& m, const double* u, const double* v, double* parts,
                                double* g, hipStream_t s);
@@ -144,7 +159,6 @@ hipError_t launch_resid_norm(int64_t n, const double* b, const double* q, CgStat
                              hipStream_t s);
 // K = exp(theta); changed != nullptr: *changed = 1 if any K differs from before, else 0
 hipError_t launch_exp(int64_t n, const double* th, double* K64, float* K32, int* changed, hipStream_t s);
-hipError_t launch_inv_diag(int64_t n, const double* d, double* i64, float* i32, const int* run, hipStream_t s);
 hipError_t launch_to_f32(int64_t n, const double* a, float* b, hipStream_t s);
 
 }  // namespace dg

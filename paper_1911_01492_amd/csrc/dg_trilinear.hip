@@ -728,119 +728,226 @@ __global__ __launch_bounds__(256) void k_dA_combine_trilinear(MeshArgs<double> m
 }
 
 // ---------------------------------------------------------------- diagonal
-// one block per element: G_q of every volume point into LDS, then one thread
-// per DOF sums gr_i^T G_q gr_i over the points, plus the face terms of the
-// face-layer DOFs (a_e(phi_i, phi_i) with phi_i on its own side).
-template <int N>
-__global__ __launch_bounds__(512) void k_diag_trilinear(MeshArgs<double> m, double* __restrict__ d,
-                                                        const int* run) {
-  constexpr int NN = N * N, N3 = NN * N;
-  __shared__ double G[N3][7];
-  if (run != nullptr && *run == 0) return;
-  const int64_t e = blockIdx.x;
-  const int t = threadIdx.x;
-  const Tables<double>& T = *m.tab;
-  double X[8][3];
-  element_corners(m, e, X);
-  const double K = m.K[e];
-  if (t < N3) {
-    const int q1 = t % N, q2 = (t / N) % N, q3 = t / NN;
-    const double xi[3] = {T.gx[q1], T.gx[q2], T.gx[q3]};
-    double J[3][3], Aj[3][3];
-    trilinear_jacobian(X, xi, J);
+// diag(A)_i = a(phi_i, phi_i) by sum factorisation: phi_i is a product of 1D
+// basis functions, so every term of the quadrature of a(phi_i, phi_i) is a
+// point factor times a product of one 1D table entry per axis, with the
+// tables of products BB, BD, DD of basis values and derivatives:
+//   volume  sum_q sum_{r<=s} (2 - [r=s]) G_rs(q) T_x T_y T_z,  T_a = DD on the
+//           axis r = s, BD on the two axes r != s, BB elsewhere (+ c w |det J| BB BB BB)
+//   face    (end layer along D only, where phi_i != 0)
+//           w (sigma gamma |N| -+ gamma l'(end) c_D) BB BB -+ w gamma (c_a BD BB + c_b BB BD),
+//           c = adj(J) N / det J the conormal; on a Dirichlet face gamma -> K
+//           and the flux terms twice, outward.
+// n^2 threads per element as in the apply: the six factors of a z-line are
+// formed from the line's Jacobian and contracted along z in registers, then
+// along y and x through LDS, grouped by their x table.  Summing all n^3
+// points for every DOF instead (6 n^3 multiply-adds per DOF) took 144 ms
+// against 1.20 ms on 48^3 Q7, and 1102 against 43 us on 23 x 18 x 21 Q4, now
+// with both inverses written in the same pass.
+template <int N, int D>
+__device__ void diag_face(const MeshArgs<double>& m, const Tables<double>& T, int64_t e, int ex, int ey, int ez,
+                          const double (&X)[8][3], double K, int t1, int t2, double* Y, double (*F)[N * N], bool act,
+                          int s) {
+  constexpr int NN = N * N, A = D == 0 ? 1 : 0, B = D == 2 ? 1 : 2, c1 = (D + 1) % 3, c2 = (D + 2) % 3;
+  const int t = t1 + N * t2;
+  const int end = s ? N - 1 : 0;
+  elem_sync<N>();  // face rows free, Y complete
+  if (act) {
+    const int64_t nb = neighbour<D>(m, ex, ey, ez, s);
+    const bool self = nb == e;  // one element along D, periodic
+    const double w = T.gw[t1] * T.gw[t2], sig = m.sig_hat / (D == 0 ? m.hx : (D == 1 ? m.hy : m.hz));
+    double J[3][3], Aj[3][3], Jo[3][3], Ao[3][3];
+    face_jacobian<D>(X, s, T.gx[t1], T.gx[t2], J);
     adj3(J, Aj);
-    const double c = T.gw[q1] * T.gw[q2] * T.gw[q3] * K / fabs(det3(J));
-    int k = 0;
-    for (int r = 0; r < 3; ++r)
-      for (int cc = r; cc < 3; ++cc)
-        G[t][k++] = c * (Aj[r][0] * Aj[cc][0] + Aj[r][1] * Aj[cc][1] + Aj[r][2] * Aj[cc][2]);
-    G[t][6] = m.R ? m.R[e] * T.gw[q1] * T.gw[q2] * T.gw[q3] * fabs(det3(J)) : 0.0;  // reaction
+    const double idet = 1.0 / det3(J);
+    double cDo = 0.0;
+    const bool other = self && s == 0;  // N dS is the upper side's
+    if (self) {
+      face_jacobian<D>(X, 1 - s, T.gx[t1], T.gx[t2], Jo);
+      adj3(Jo, Ao);
+    }
+    double Nv[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const int p = (r + 1) % 3, q = (r + 2) % 3;
+      Nv[r] = other ? Jo[p][c1] * Jo[q][c2] - Jo[q][c1] * Jo[p][c2] : J[p][c1] * J[q][c2] - J[q][c1] * J[p][c2];
+    }
+    const double area = sqrt(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
+    double c[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) c[r] = (Aj[r][0] * Nv[0] + Aj[r][1] * Nv[1] + Aj[r][2] * Nv[2]) * idet;
+    // the other side of the element's own face: its normal derivative at the
+    // end node (its trace there is zero)
+    if (self) cDo = (Ao[D][0] * Nv[0] + Ao[D][1] * Nv[1] + Ao[D][2] * Nv[2]) / det3(Jo) * (s ? T.d0 : T.d1)[end];
+    double gam = K;
+    double fl = s ? -2.0 * K : 2.0 * K;  // Dirichlet: both flux terms, outward normal
+    if (nb >= 0) {
+      const double Kn = m.K[nb];
+      gam = 2.0 * K * Kn / (K + Kn);
+      fl = s ? -gam : gam;  // [phi] = phi on the upper face, -phi on the lower
+    }
+    F[0][t] = w * (sig * gam * area + fl * ((s ? T.d1 : T.d0)[end] * c[D] + cDo));
+    F[1][t] = w * fl * c[A];
+    F[2][t] = w * fl * c[B];
   }
-  __syncthreads();  // G is shared by the whole block
-  if (t >= N3) return;
-  const int i1 = t % N, i2 = (t / N) % N, i3 = t / NN;
-  const int ii[3] = {i1, i2, i3};
-  double acc = 0.0;
-  for (int q3 = 0; q3 < N; ++q3)
-    for (int q2 = 0; q2 < N; ++q2)
-      for (int q1 = 0; q1 < N; ++q1) {
-        const double b1 = T.B[q1 * kMaxN + i1], b2 = T.B[q2 * kMaxN + i2], b3 = T.B[q3 * kMaxN + i3];
-        const double g0 = T.D[q1 * kMaxN + i1] * b2 * b3;
-        const double g1 = b1 * T.D[q2 * kMaxN + i2] * b3;
-        const double g2 = b1 * b2 * T.D[q3 * kMaxN + i3];
-        const double* Gq = G[q1 + N * (q2 + N * q3)];
-        acc += Gq[0] * g0 * g0 + Gq[3] * g1 * g1 + Gq[5] * g2 * g2 +
-               2.0 * (Gq[1] * g0 * g1 + Gq[2] * g0 * g2 + Gq[4] * g1 * g2) + Gq[6] * (b1 * b2 * b3) * (b1 * b2 * b3);
+  elem_sync<N>();
+  if (act) {  // along t1: BB F0 + BD F1 and BB F2
+    double r0 = 0.0, r1 = 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const double bb = T.BB[q * kMaxN + t1], bd = T.BD[q * kMaxN + t1];
+      r0 += bb * F[0][t2 * N + q] + bd * F[1][t2 * N + q];
+      r1 += bb * F[2][t2 * N + q];
+    }
+    F[3][t] = r0;
+    F[4][t] = r1;
+  }
+  elem_sync<N>();
+  if (act) {  // along t2, into the end layer
+    double r = 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) r += T.BB[q * kMaxN + t2] * F[3][q * N + t1] + T.BD[q * kMaxN + t2] * F[4][q * N + t1];
+    Y[lds_idx<N, D, double>(t1, t2, end)] += r;
+  }
+  (void)NN;
+}
+
+// out_i (+)= sum_q T_qi a_q along the line (T: one of the product tables)
+template <int N, bool ADD>
+__device__ __forceinline__ void prod_line(const double* T, const double (&a)[N], double (&out)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    double s = ADD ? out[i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) s += T[q * kMaxN + i] * a[q];
+    out[i] = s;
+  }
+}
+
+template <int N>
+__global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, DiagOut out, const int* run) {
+  constexpr int NN = N * N, N3 = NN * N, EPB = elems_per_block(N), PE = Lay<N, double>::PE;
+  static_assert(5 * NN <= 2 * PE, "the face rows share two tiles");
+  __shared__ double sT[EPB * 3 * PE];
+  __shared__ double sX[EPB][8][3];
+  if (run != nullptr && *run == 0) return;
+  const Tables<double>& T = *m.tab;
+  const int tid = threadIdx.x, el = tid / NN, t = tid % NN, t1 = t % N, t2 = t / N;
+  const int64_t e = (int64_t)blockIdx.x * EPB + el;
+  const bool act = (el < EPB) && (e < m.E);
+  const int le = act ? el : 0;
+  double* A = sT + le * 3 * PE;
+  double* B = A + PE;
+  double* C = B + PE;
+  double(*F)[NN] = (double(*)[NN])B;
+  int ex = 0, ey = 0, ez = 0;
+  double K = 1.0;
+  if (act) {
+    ex = (int)(e % m.nx);
+    ey = (int)((e / m.nx) % m.ny);
+    ez = (int)(e / ((int64_t)m.nx * m.ny));
+    K = m.K[e];
+    for (int q = t; q < 24; q += NN) corner_at(m, ex, ey, ez, q / 3, q % 3, sX[le][q / 3][q % 3]);
+  }
+  elem_sync<N>();
+  const double(&X)[8][3] = sX[le];
+  // z-lines contracted along z: a00, a01, a11 with BB, a02, a12 with BD (the
+  // factors 2 of the mixed terms here), a22 with DD joined by the reaction
+  double a00[N], a01[N], a02[N], a11[N], a12[N], a22[N];
+  if (act) {
+    const JacZLine<double> jz(X, T.gx[t1], T.gx[t2]);
+    const double wq = T.gw[t1] * T.gw[t2] * K, cw = m.R ? m.R[e] * T.gw[t1] * T.gw[t2] : 0.0;
+#pragma unroll
+    for (int i = 0; i < N; ++i) a00[i] = a01[i] = a02[i] = a11[i] = a12[i] = a22[i] = 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      double J[3][3], Aj[3][3];
+      jz.at(T.gx[q], J);
+      adj3(J, Aj);
+      const double dJ = fabs(det3(J)), c = wq * T.gw[q] / dJ, cr = cw * T.gw[q] * dJ;
+      auto G = [&](int r, int s2) { return c * (Aj[r][0] * Aj[s2][0] + Aj[r][1] * Aj[s2][1] + Aj[r][2] * Aj[s2][2]); };
+      const double g00 = G(0, 0), g01 = 2.0 * G(0, 1), g02 = 2.0 * G(0, 2), g11 = G(1, 1), g12 = 2.0 * G(1, 2),
+                   g22 = G(2, 2);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const double bb = T.BB[q * kMaxN + i], bd = T.BD[q * kMaxN + i], dd = T.DD[q * kMaxN + i];
+        a00[i] += bb * g00;
+        a01[i] += bb * g01;
+        a11[i] += bb * g11;
+        a02[i] += bd * g02;
+        a12[i] += bd * g12;
+        a22[i] += dd * g22 + bb * cr;
       }
-  const int ex = (int)(e % m.nx), ey = (int)((e / m.nx) % m.ny), ez = (int)(e / ((int64_t)m.nx * m.ny));
-  for (int D = 0; D < 3; ++D) {
-    const int ax = (D == 0) ? 1 : 0, bx = (D == 2) ? 1 : 2;
-    const int c1 = (D + 1) % 3, c2 = (D + 2) % 3;
-    const double h = D == 0 ? m.hx : (D == 1 ? m.hy : m.hz);
-    const double sig = m.sig_hat / h;
-    for (int s = 0; s < 2; ++s) {
-      int64_t nb;
-      if (D == 0) nb = neighbour<0>(m, ex, ey, ez, s);
-      else if (D == 1) nb = neighbour<1>(m, ex, ey, ez, s);
-      else nb = neighbour<2>(m, ex, ey, ez, s);
-      const bool self = (nb == e);
-      if (self && s == 0) continue;  // the element's own periodic face: once
-      const int end = s ? N - 1 : 0;
-      if (!self && ii[D] != end) continue;
-      double gam = K;
-      if (nb >= 0) {
-        const double Kn = m.K[nb];
-        gam = 2.0 * K * Kn / (K + Kn);
-      }
-      for (int qb = 0; qb < N; ++qb)
-        for (int qa = 0; qa < N; ++qa) {
-          const double w = T.gw[qa] * T.gw[qb];
-          // value and physical gradient of phi_i on this element at xi_D = side
-          auto eval = [&](int side, double& val, double (&g)[3], double (&Jc)[3][3]) {
-            double xi[3];
-            xi[D] = side;
-            xi[ax] = T.gx[qa];
-            xi[bx] = T.gx[qb];
-            double Aj[3][3];
-            trilinear_jacobian(X, xi, Jc);
-            adj3(Jc, Aj);
-            const double det = det3(Jc);
-            const double* dE = side ? T.d1 : T.d0;
-            const double la = T.B[qa * kMaxN + ii[ax]], lb = T.B[qb * kMaxN + ii[bx]];
-            const double le = (ii[D] == (side ? N - 1 : 0)) ? 1.0 : 0.0;
-            val = le * la * lb;
-            double gr[3];
-            gr[D] = dE[ii[D]] * la * lb;
-            gr[ax] = le * T.D[qa * kMaxN + ii[ax]] * lb;
-            gr[bx] = le * la * T.D[qb * kMaxN + ii[bx]];
-            for (int c = 0; c < 3; ++c) g[c] = (Aj[0][c] * gr[0] + Aj[1][c] * gr[1] + Aj[2][c] * gr[2]) / det;
-          };
-          double v1, gA[3], J1[3][3];
-          eval(s, v1, gA, J1);
-          double Nv[3];
-          Nv[0] = J1[1][c1] * J1[2][c2] - J1[2][c1] * J1[1][c2];
-          Nv[1] = J1[2][c1] * J1[0][c2] - J1[0][c1] * J1[2][c2];
-          Nv[2] = J1[0][c1] * J1[1][c2] - J1[1][c1] * J1[0][c2];
-          const double area = sqrt(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
-          if (self) {  // phi_i on both sides of the face: [phi] = phi(1) - phi(0)
-            double v0, gB[3], J0[3][3];
-            eval(0, v0, gB, J0);
-            const double jump = v1 - v0;
-            const double avg = 0.5 * gam * ((gA[0] + gB[0]) * Nv[0] + (gA[1] + gB[1]) * Nv[1] + (gA[2] + gB[2]) * Nv[2]);
-            acc += w * (-2.0 * avg * jump + sig * gam * area * jump * jump);
-          } else if (nb >= 0) {
-            const double fl = gA[0] * Nv[0] + gA[1] * Nv[1] + gA[2] * Nv[2];
-            const double sg = s ? -1.0 : 1.0;  // [phi] = +phi on the upper face, -phi on the lower
-            acc += w * (sg * gam * fl * v1 + sig * gam * area * v1 * v1);
-          } else {
-            const double sg = s ? 1.0 : -1.0;  // outward normal
-            const double fl = sg * (gA[0] * Nv[0] + gA[1] * Nv[1] + gA[2] * Nv[2]);
-            acc += w * (-2.0 * K * fl * v1 + sig * K * area * v1 * v1);
-          }
-        }
     }
   }
-  d[e * N3 + t] = acc;
+  double acc[N], v[N], w[N];
+  // x table DD: a00 (y: BB)
+  if (act) lds_put<N, 2>(A, t1, t2, a00);
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 1>(A, t1, t2, v);
+    prod_line<N, false>(T.BB, v, w);
+    lds_put<N, 1>(A, t1, t2, w);
+  }
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 0>(A, t1, t2, v);
+    prod_line<N, false>(T.DD, v, acc);
+  }
+  elem_sync<N>();
+  // x table BD: a01 (y: BD) + a02 (y: BB)
+  if (act) {
+    lds_put<N, 2>(A, t1, t2, a01);
+    lds_put<N, 2>(B, t1, t2, a02);
+  }
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 1>(A, t1, t2, v);
+    prod_line<N, false>(T.BD, v, w);
+    lds_get<N, 1>(B, t1, t2, v);
+    prod_line<N, true>(T.BB, v, w);
+    lds_put<N, 1>(A, t1, t2, w);
+  }
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 0>(A, t1, t2, v);
+    prod_line<N, true>(T.BD, v, acc);
+  }
+  elem_sync<N>();
+  // x table BB: a11 (y: DD) + a12 (y: BD) + a22 (y: BB)
+  if (act) {
+    lds_put<N, 2>(A, t1, t2, a11);
+    lds_put<N, 2>(B, t1, t2, a12);
+    lds_put<N, 2>(C, t1, t2, a22);
+  }
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 1>(A, t1, t2, v);
+    prod_line<N, false>(T.DD, v, w);
+    lds_get<N, 1>(B, t1, t2, v);
+    prod_line<N, true>(T.BD, v, w);
+    lds_get<N, 1>(C, t1, t2, v);
+    prod_line<N, true>(T.BB, v, w);
+    lds_put<N, 1>(A, t1, t2, w);
+  }
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 0>(A, t1, t2, v);
+    prod_line<N, true>(T.BB, v, acc);
+    lds_put<N, 0>(A, t1, t2, acc);  // the thread's own x-line
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    diag_face<N, 0>(m, T, e, ex, ey, ez, X, K, t1, t2, A, F, act, s);
+    diag_face<N, 1>(m, T, e, ex, ey, ez, X, K, t1, t2, A, F, act, s);
+    diag_face<N, 2>(m, T, e, ex, ey, ez, X, K, t1, t2, A, F, act, s);
+  }
+  elem_sync<N>();
+  if (act) {
+    lds_get<N, 2>(A, t1, t2, v);
+#pragma unroll
+    for (int i = 0; i < N; ++i) out.put(e * N3 + lidx<N, 2>(t1, t2, i), v[i]);
+  }
 }
 
 // ---------------------------------------------------------------- launchers
@@ -899,9 +1006,8 @@ hipError_t launch_apply_trilinear(int n, int prec, int trans, int dot, const Mes
 }
 
 template <int N>
-static hipError_t run_tri_diag(const MeshArgs<double>& m, double* d, const int* run, hipStream_t s) {
-  const int th = ((N * N * N + 63) / 64) * 64;
-  hipLaunchKernelGGL((k_diag_trilinear<N>), dim3((unsigned)m.E), dim3(th), 0, s, m, d, run);
+static hipError_t run_tri_diag(const MeshArgs<double>& m, const DiagOut& d, const int* run, hipStream_t s) {
+  hipLaunchKernelGGL((k_diag_trilinear<N>), dim3((unsigned)element_blocks(N, m.E)), dim3(kBlock), 0, s, m, d, run);
   return hipGetLastError();
 }
 template <int N>
@@ -929,7 +1035,7 @@ hipError_t launch_dA_trilinear(int n, const MeshArgs<double>& m, const double* u
   }
 }
 
-hipError_t launch_diag_trilinear(int n, const MeshArgs<double>& m, double* d, const int* run, hipStream_t s) {
+hipError_t launch_diag_trilinear(int n, const MeshArgs<double>& m, const DiagOut& d, const int* run, hipStream_t s) {
   switch (n) {
     case 2: return run_tri_diag<2>(m, d, run, s);
     case 3: return run_tri_diag<3>(m, d, run, s);

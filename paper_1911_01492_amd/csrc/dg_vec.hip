@@ -726,16 +726,6 @@ __global__ void k_exp(int64_t n, const double* __restrict__ th, double* __restri
 __global__ void k_set_flag(int* f, int v) {
   if (threadIdx.x == 0) *f = v;
 }
-// run != nullptr && *run == 0: nothing to do (the diagonal is unchanged)
-__global__ void k_inv_diag(int64_t n, const double* __restrict__ d, double* __restrict__ i64,
-                           float* __restrict__ i32, const int* run) {
-  if (run != nullptr && *run == 0) return;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double v = 1.0 / d[i];
-  i64[i] = v;
-  i32[i] = (float)v;
-}
 __global__ void k_to_f32(int64_t n, const double* __restrict__ a, float* __restrict__ b) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) b[i] = (float)a[i];
@@ -748,10 +738,6 @@ hipError_t launch_exp(int64_t n, const double* th, double* K64, float* K32, int*
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_exp, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, th, K64, K32, changed);
-  return hipGetLastError();
-}
-hipError_t launch_inv_diag(int64_t n, const double* d, double* i64, float* i32, const int* run, hipStream_t s) {
-  hipLaunchKernelGGL(k_inv_diag, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, d, i64, i32, run);
   return hipGetLastError();
 }
 hipError_t launch_to_f32(int64_t n, const double* a, float* b, hipStream_t s) {
