@@ -10,38 +10,6 @@
 
 namespace dg {
 
-template <typename T>
-__device__ __forceinline__ void element_corners(const MeshArgs<T>& m, int64_t e, T (&X)[8][3]) {
-  const int ex = (int)(e % m.nx), ey = (int)((e / m.nx) % m.ny), ez = (int)(e / ((int64_t)m.nx * m.ny));
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const int vx = ex + (c & 1), vy = ey + ((c >> 1) & 1), vz = ez + ((c >> 2) & 1);
-    if (m.vert) {
-      const int64_t v = vx + (int64_t)(m.nx + 1) * (vy + (int64_t)(m.ny + 1) * vz);
-      X[c][0] = m.vert[3 * v];
-      X[c][1] = m.vert[3 * v + 1];
-      X[c][2] = m.vert[3 * v + 2];
-    } else {
-      X[c][0] = (T)vx * m.hx;
-      X[c][1] = (T)vy * m.hy;
-      X[c][2] = (T)vz * m.hz;
-    }
-  }
-}
-
-// x = F(xi) = sum_c X_c prod_d (c_d ? xi_d : 1 - xi_d)
-template <typename T>
-__device__ __forceinline__ void trilinear_map(const T (&X)[8][3], const T (&xi)[3], T (&x)[3]) {
-  x[0] = x[1] = x[2] = T(0);
-#pragma unroll
-  for (int c = 0; c < 8; ++c) {
-    const T w = ((c & 1) ? xi[0] : T(1) - xi[0]) * ((c & 2) ? xi[1] : T(1) - xi[1]) *
-                ((c & 4) ? xi[2] : T(1) - xi[2]);
-#pragma unroll
-    for (int a = 0; a < 3; ++a) x[a] += w * X[c][a];
-  }
-}
-
 // J[a][d] = d x_a / d xi_d, written with the edge vectors of the corner cube:
 // dF/dxi_0 = (1-xi_1)(1-xi_2)(X1-X0) + xi_1(1-xi_2)(X3-X2) + (1-xi_1)xi_2(X5-X4) + xi_1 xi_2 (X7-X6)
 // and cyclically for the other two directions.
