@@ -34,6 +34,7 @@
 #include "dg_kernels.hpp"
 #include "dg_lines.hpp"
 #include "dg_faces.hpp"
+#include "dg_tables.hpp"
 
 namespace dg {
 
@@ -141,7 +142,16 @@ __global__ __launch_bounds__(apply_block(N), (N == 5 && sizeof(TC) == 8) ? 8 : 1
   // so no slot of their own is needed
   constexpr int SLOTS = TE;
   static_assert(TE * NN == BLOCK || BLOCK - (TE - 1) * NN <= 64, "padding lanes and their twins share a wavefront");
+  // FP32 at n = 3..7: x is loaded once, as z-lines (whose lanes are adjacent in
+  // memory), into a tile of its own that all three orientations read, instead
+  // of three times with the lanes of the x- and y-lines n and n^2 values apart
+  // (at n = 5 in FP64 the texture path is busy 96% of the time with these).
+  // 58^3 Q4 FP32 98 -> 88 us, BF16 86 -> 79, 42^3 Q6 FP32 108 -> 99.  In FP64
+  // the tile's LDS traffic costs more than it saves (73^3 Q3 152 -> 168 us),
+  // and so does its space at n = 8 in FP32 (37^3 Q7 79 -> 90).
+  constexpr bool STAGED = sizeof(TC) == 4 && N >= 3 && N <= 7;
   __shared__ TC sS1[SLOTS * PE], sS2[SLOTS * PE];
+  __shared__ TC sU[STAGED ? SLOTS * PE : 1];
   __shared__ TC sFx[F_IN_S2 ? 1 : SLOTS * 4 * NN];
   __shared__ double red[BLOCK / 64];
   if (skip != nullptr && *skip) return;
@@ -149,12 +159,20 @@ __global__ __launch_bounds__(apply_block(N), (N == 5 && sizeof(TC) == 8) ? 8 : 1
   x += (size_t)blockIdx.y * (size_t)m.E * N3;
   y += (size_t)blockIdx.y * (size_t)m.E * N3;
   TC* F = F_IN_S2 ? sS2 : sFx;
-  // The 1D tables are read through the scalar cache.  At n = 8 in FP64 they
-  // do not fit in scalar registers for the whole kernel (the compiler spills
-  // them into vector-register lanes): there each use re-derives their address
-  // through a constant-address pointer, so each phase loads what it uses.
-  auto tabs = [&]() -> const Tables<TC>& {
-    if constexpr (N >= 8 && sizeof(TC) == 8) {
+  // The 1D tables.  FP32 from n = 3: compile-time constants, which become
+  // literals of the instructions (no table loads to wait for; 64^3 Q4 BF16 3%,
+  // 20^3 Q7 FP32 12% faster; at n = 2 13% slower).  FP64 literals would take
+  // two scalar moves each (0-7% slower), so there the tables are read through
+  // the scalar cache; at n = 8 they do not fit in scalar registers for the whole
+  // kernel (the compiler spills them into vector-register lanes) and each use
+  // re-derives their address through a constant-address pointer, so each phase
+  // loads what it uses.
+  constexpr bool CTAB = sizeof(TC) == 4 && N >= 3;
+  [[maybe_unused]] constexpr KTables<TC> ktab = CTAB ? ctab::make<N, TC>() : KTables<TC>{};
+  auto tabs = [&]() -> decltype(auto) {
+    if constexpr (CTAB) {
+      return (ktab);
+    } else if constexpr (N >= 8) {
       uint64_t a = (uint64_t)m.tab;
       asm volatile("" : "+s"(a));
       typedef const __attribute__((address_space(4))) Tables<TC>* ConstTab;
@@ -193,12 +211,20 @@ __global__ __launch_bounds__(apply_block(N), (N == 5 && sizeof(TC) == 8) ? 8 : 1
   // that uses them (keeps the register count at 64 for n = 5 in FP64)
   auto gco = [&](int f) { return OFF32 ? m.G[(uint32_t)(6 * e + f)] : m.G[6 * e + f]; };
   TC b[N], v[N], w[N];
+  const TC* U = sU + (STAGED ? le * PE : 0);
+  if constexpr (STAGED) {
+    glb_get_at<N, 2, TC, TIN, OFF32>(x, eo, t1, t2, v);
+    lds_put<N, 2, TC, LV>(sU + le * PE, t1, t2, v);
+    lds_sync<ELEM>();
+  }
   // ---------------- X: b_x -> S1
-  face_phase<N, 0, BX, BY, BZ, FS, TC, TIN, TRANS, OFF32>(m, tabs(), x, own, eo, c, o, Nd, t, t1, t2, Fe, K, gco(0), gco(1), TC(0), b);
+  face_phase<N, 0, BX, BY, BZ, FS, TC, TIN, TRANS, OFF32, STAGED, LV>(m, tabs(), x, own, eo, c, o, Nd, t, t1, t2, Fe, K,
+                                                                     gco(0), gco(1), TC(0), b, nullptr, nullptr, U);
   lds_put<N, 0, TC, LV>(S1, t1, t2, b);
   lds_sync<XROW>();  // F (read by the x-neighbours) is rewritten by the next phase
   // ---------------- Y: b_y -> S2, M_y b_x -> S1
-  face_phase<N, 1, BX, BY, BZ, FS, TC, TIN, TRANS, OFF32>(m, tabs(), x, own, eo, c, o, Nd, t, t1, t2, Fe, K, gco(2), gco(3), TC(0), b);
+  face_phase<N, 1, BX, BY, BZ, FS, TC, TIN, TRANS, OFF32, STAGED, LV>(m, tabs(), x, own, eo, c, o, Nd, t, t1, t2, Fe, K,
+                                                                     gco(2), gco(3), TC(0), b, nullptr, nullptr, U);
   {
     lds_get<N, 1, TC, LV>(S1, t1, t2, v);
     mass_line<N, TC, TRANS>(tabs(), v, w);
@@ -222,8 +248,9 @@ __global__ __launch_bounds__(apply_block(N), (N == 5 && sizeof(TC) == 8) ? 8 : 1
   // ---------------- Z: b_z -> S2, r = M_z S1
   TC r[N], xz[N];  // xz: the thread's z-line of x, for the fused <x, y>
   const TC cr = m.R ? m.R[e] * m.vol : TC(0);
-  face_phase<N, 2, BX, BY, BZ, FS, TC, TIN, TRANS, OFF32>(m, tabs(), x, own, eo, c, o, Nd, t, t1, t2, Fe, K, gco(4), gco(5), cr, b,
-                                               DOT ? xz : nullptr);
+  face_phase<N, 2, BX, BY, BZ, FS, TC, TIN, TRANS, OFF32, STAGED, LV>(m, tabs(), x, own, eo, c, o, Nd, t, t1, t2, Fe, K,
+                                                                     gco(4), gco(5), cr, b, DOT ? xz : nullptr, nullptr,
+                                                                     U);
   {
     lds_get<N, 2, TC, LV>(S1, t1, t2, v);
     mass_line<N, TC, TRANS>(tabs(), v, r);
@@ -251,13 +278,11 @@ __global__ __launch_bounds__(apply_block(N), (N == 5 && sizeof(TC) == 8) ? 8 : 1
     // y is written once and not read back here: nontemporal stores keep it
     // from displacing in L2 the x lines that neighbouring bricks still read
     const uint32_t yb = (eo + (uint32_t)lidx<N, 2>(t1, t2, 0)) * (uint32_t)sizeof(TOUT);
-    TOUT* py = y + e * N3;
+    TOUT* py = OFF32 ? (TOUT*)((char*)y + (size_t)yb) : y + e * N3 + lidx<N, 2>(t1, t2, 0);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const TOUT yv = (TOUT)(r[i] + v[i]);
-      TOUT* dst = OFF32 ? (TOUT*)((char*)y + (yb + (uint32_t)(lidx<N, 2>(0, 0, i) * sizeof(TOUT))))
-                        : &py[lidx<N, 2>(t1, t2, i)];
-      __builtin_nontemporal_store(yv, dst);
+      __builtin_nontemporal_store(yv, py + lidx<N, 2>(0, 0, i));
       if (DOT) part += (double)xz[i] * (double)yv;
     }
   }

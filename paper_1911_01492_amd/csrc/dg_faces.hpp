@@ -52,7 +52,8 @@ struct AxisNeighbours {
   }
   // the HBM neighbour lines reduced to their face scalars (frees the lines)
   TC uL, dL, uH, dH;
-  __device__ __forceinline__ void reduce(const Tables<TC>& T) {
+  template <typename TT>
+  __device__ __forceinline__ void reduce(const TT& T) {
     uL = dL = uH = dH = TC(0);
     if (glL) {
       uL = gL[N - 1];
@@ -99,23 +100,26 @@ __device__ __forceinline__ void lds_sync() {
 }
 
 // One face-aware direction of the affine apply: b = L_D u on this thread's
-// line along axis D (own line from HBM, neighbour face scalars from the
-// brick's exchange area or from HBM; Fe: the element's own slot in that
-// area).  Contains one barrier; every thread of the block calls it.
+// line along axis D (own line from HBM, or STAGED: from the element's LDS tile
+// U, layout LV; neighbour face scalars from the brick's exchange area or from
+// HBM; Fe: the element's own slot in that area).  Contains one barrier; every thread of the block calls it.
 // act == false: the lane's element overhangs the mesh (it computes on a
 // clamped element, sees no neighbours, and its result is discarded).
-template <int N, int D, int BX, int BY, int BZ, int FS, typename TC, typename TIN, bool TRANS, bool OFF32>
-__device__ __forceinline__ void face_phase(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN* __restrict__ x,
+template <int N, int D, int BX, int BY, int BZ, int FS, typename TC, typename TIN, bool TRANS, bool OFF32,
+          bool STAGED = false, int LV = 0, typename TT>
+__device__ __forceinline__ void face_phase(const MeshArgs<TC>& m, const TT& T, const TIN* __restrict__ x,
                                            bool act, uint32_t eo, const int (&c)[3], const int (&o)[3],
                                            const int (&Nd)[3], int t, int t1, int t2, TC* Fe, TC K, TC GL,
-                                           TC GH, TC cr, TC (&b)[N], TC* own = nullptr, TC* nbt = nullptr) {
+                                           TC GH, TC cr, TC (&b)[N], TC* own = nullptr, TC* nbt = nullptr,
+                                           const TC* U = nullptr) {
   constexpr int NN = N * N;
   AxisNeighbours<N, D, BX, BY, BZ, TC, TIN, OFF32> nb;
   TC u[N], g0, g1;
   {
     nb.template locate<FS>(m.nx, m.ny, eo, c, o, Nd, m.periodic, act);
     nb.fetch(x, t1, t2);
-    glb_get_at<N, D, TC, TIN, OFF32>(x, eo, t1, t2, u);
+    if constexpr (STAGED) lds_get<N, D, TC, LV>(U, t1, t2, u);
+    else glb_get_at<N, D, TC, TIN, OFF32>(x, eo, t1, t2, u);
     nb.reduce(T);
     g0 = dot_end<N, TC, 0>(T, u);
     g1 = dot_end<N, TC, 1>(T, u);

@@ -89,10 +89,11 @@ template <int N, int D, typename TC, typename TIN, bool OFF32 = false>
 __device__ __forceinline__ void glb_get_at(const TIN* __restrict__ x, uint32_t eo, int t1, int t2, TC (&v)[N]) {
   // eo: the element's first entry (element index times n^3)
   if constexpr (OFF32) {
-    const uint32_t b = (eo + (uint32_t)lidx<N, D>(t1, t2, 0)) * (uint32_t)sizeof(TIN);
+    // (the value index goes into the instruction's immediate offset, and the
+    // adjacent values of an x-line merge into wider loads)
+    const TIN* p = (const TIN*)((const char*)x + (size_t)((eo + (uint32_t)lidx<N, D>(t1, t2, 0)) * (uint32_t)sizeof(TIN)));
 #pragma unroll
-    for (int i = 0; i < N; ++i)
-      v[i] = load_as<TC, TIN>((const TIN*)((const char*)x + (b + (uint32_t)(lidx<N, D>(0, 0, i) * sizeof(TIN)))));
+    for (int i = 0; i < N; ++i) v[i] = load_as<TC, TIN>(p + lidx<N, D>(0, 0, i));
   } else {
     const uint32_t base = eo + (uint32_t)lidx<N, D>(t1, t2, 0);
 #pragma unroll
@@ -156,9 +157,10 @@ __device__ __forceinline__ void sym_line(const TC* Af, const EvenOdd<TC>& Ae, co
   }
 }
 
-// out = M a along the line (M is symmetric: also M^T a)
-template <int N, typename TC, bool TRANS>
-__device__ __forceinline__ void mass_line(const Tables<TC>& T, const TC (&a)[N], TC (&out)[N]) {
+// out = M a along the line (M is symmetric: also M^T a); T here and below: the
+// tables in memory (Tables) or as constants (KTables)
+template <int N, typename TC, bool TRANS, typename TT>
+__device__ __forceinline__ void mass_line(const TT& T, const TC (&a)[N], TC (&out)[N]) {
   sym_line<N, TC>(T.M, T.eM, a, out);
 }
 
@@ -167,8 +169,8 @@ __device__ __forceinline__ void mass_line(const Tables<TC>& T, const TC (&a)[N],
 // derivative at that end (Gr = l'(end) . line, without 1/h), both zero on a
 // side without neighbour (Dirichlet face).  Own face scalars: u[0],
 // g0 = d0.u, u[n-1], g1 = d1.u.  Same algebra as line_op.
-template <int N, typename TC, bool TRANS>
-__device__ __forceinline__ void line_op_s(const Tables<TC>& T, const TC (&u)[N], TC g0, TC g1, TC UL, TC GLr,
+template <int N, typename TC, bool TRANS, typename TT>
+__device__ __forceinline__ void line_op_s(const TT& T, const TC (&u)[N], TC g0, TC g1, TC UL, TC GLr,
                                           TC UH, TC GHr, bool hasL, bool hasH, TC GL, TC GH, TC vs, TC ih,
                                           TC sig, TC At, TC (&b)[N]) {
   {  // volume: vs S u (S is symmetric: also the transpose)
@@ -200,8 +202,8 @@ __device__ __forceinline__ void line_op_s(const Tables<TC>& T, const TC (&u)[N],
 }
 
 // d0 . u (END = 0) or d1 . u (END = 1)
-template <int N, typename TC, int END>
-__device__ __forceinline__ TC dot_end(const Tables<TC>& T, const TC (&u)[N]) {
+template <int N, typename TC, int END, typename TT>
+__device__ __forceinline__ TC dot_end(const TT& T, const TC (&u)[N]) {
   TC s = TC(0);
 #pragma unroll
   for (int j = 0; j < N; ++j) s += (END ? T.d1[j] : T.d0[j]) * u[j];
