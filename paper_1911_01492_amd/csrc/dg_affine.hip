@@ -803,6 +803,10 @@ int64_t affine_tiles(int n, int nx, int ny, int nz) {
   return (int64_t)((nx + bx - 1) / bx) * ((ny + by - 1) / by) * ((nz + bz - 1) / bz);
 }
 
+int64_t affine_partials(int n, int prec, int nx, int ny, int nz) {
+  return use_planes(n, prec, (int64_t)nx * ny * nz) ? plane_blocks(n, nx, ny, nz) : affine_tiles(n, nx, ny, nz);
+}
+
 template <int N, typename TIN, typename TOUT, typename TC, bool TRANS, bool DOT>
 static hipError_t run_apply(const MeshArgs<TC>& m, const void* x, void* y, double* partials, CgState* st,
                             int par, const int* skip, hipStream_t s, int nrhs = 1) {
@@ -856,6 +860,11 @@ static hipError_t run_apply_n(int prec, int trans, int dot, const MeshArgs<doubl
 hipError_t launch_apply_affine(int n, int prec, int trans, int dot, const MeshArgs<double>& m64,
                                const MeshArgs<float>& m32, const void* x, void* y, double* partials,
                                CgState* st, int par, const int* skip, hipStream_t s) {
+  if (use_planes(n, prec, m64.E)) {  // the operator is symmetric: trans is the same product
+    const hipError_t e = launch_apply_planes(n, prec, dot, m64, m32, x, y, partials, skip, s);
+    if (e != hipSuccess || !dot || st == nullptr) return e;
+    return launch_finish_dot(partials, plane_blocks(n, m64.nx, m64.ny, m64.nz), st, par, s);
+  }
   switch (n) {
     case 2: return run_apply_n<2>(prec, trans, dot, m64, m32, x, y, partials, st, par, skip, s);
     case 3: return run_apply_n<3>(prec, trans, dot, m64, m32, x, y, partials, st, par, skip, s);
@@ -927,6 +936,7 @@ static hipError_t run_multi_n(int prec, int trans, int nrhs, const MeshArgs<doub
 }
 hipError_t launch_apply_affine_multi(int n, int prec, int trans, int nrhs, const MeshArgs<double>& m64,
                                      const MeshArgs<float>& m32, const void* x, void* y, hipStream_t s) {
+  if (use_planes(n, prec, m64.E)) return launch_apply_planes(n, prec, 0, m64, m32, x, y, nullptr, nullptr, s, nrhs);
   switch (n) {
     case 2: return run_multi_n<2>(prec, trans, nrhs, m64, m32, x, y, s);
     case 3: return run_multi_n<3>(prec, trans, nrhs, m64, m32, x, y, s);

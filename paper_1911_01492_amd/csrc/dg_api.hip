@@ -528,9 +528,10 @@ MeshArgs<T> ppd_args(const dg_ctx* c, MeshArgs<T> m) {
 // breakdown check)
 // block partials of the fused <x, A x> of an apply: one per brick of the
 // affine and parallelepiped kernels, one per element block of the trilinear one
-int64_t apply_partials(const dg_ctx* c) {
+int64_t apply_partials(const dg_ctx* c, int prec) {
   if (c->trilinear && !c->ppd) return element_blocks(c->n, c->E);
-  return affine_tiles(c->n, c->desc.nx, c->desc.ny, c->desc.nz);
+  if (c->ppd) return affine_tiles(c->n, c->desc.nx, c->desc.ny, c->desc.nz);
+  return affine_partials(c->n, prec, c->desc.nx, c->desc.ny, c->desc.nz);
 }
 
 hipError_t apply_any(dg_ctx* c, int prec, int trans, int dot, const void* x, void* y, CgState* st, int par,
@@ -906,7 +907,7 @@ int pcg64(dg_ctx* c, const dg_cg_opts* o, const double* b, double* x, int maxit,
   int rc = read_state(c, 0, hs, s);
   if (rc != DG_OK) return rc;
   // few block partials: the update kernels sum them themselves (no finish kernels)
-  const int64_t nbA = apply_partials(c);
+  const int64_t nbA = apply_partials(c, DG_F64);
   const bool fused = nbA <= 4096 && 2 * vec_blocks(n) <= 8192;
   double* partA = c->partials;
   double* partB = c->partials + nbA;
@@ -958,7 +959,7 @@ int pcg64_block(dg_ctx* c, const dg_cg_opts* o, const double* b, double* x, int 
   if (rc != DG_OK) return rc;
   // few block partials: the block apply and the direction update sum them
   // themselves (no finish kernels)
-  const int64_t nbA = apply_partials(c);
+  const int64_t nbA = apply_partials(c, DG_F64);
   const bool fused = nbA <= 4096 && nbj <= 4096;
   double* partA = c->partials;
   double* partB = c->partials + nbA;
@@ -1002,7 +1003,7 @@ int pcg64_single(dg_ctx* c, const dg_cg_opts* o, const double* b, double* x, int
   const int64_t nvb = vec_blocks(n);
   double* partA = c->partials;             // <r, z>, <r, r> of the update (2 per vector block)
   double* partB = c->partials + 2 * nvb;   // <z, w> of the apply
-  const int64_t nbB = apply_partials(c);
+  const int64_t nbB = apply_partials(c, DG_F64);
   HIP_TRY(c, apply_any(c, DG_F64, o->transpose, 0, x, c->q64, nullptr, 0, nullptr, s));
   // r = b - A x0, z = Dinv r (into z), gamma = <r, z>, <r, r>, <b, b>
   HIP_TRY(c, (launch_cg_init<double, double, double, double>(n, b, c->q64, c->r64, c->z64, dinv, o->rtol, st,
@@ -1071,7 +1072,7 @@ int pcg_inner(dg_ctx* c, const dg_cg_opts* o, int prec, bool fresh, double inner
   int rc = read_state(c, 1, hs, s);
   if (rc != DG_OK) return rc;
   // few block partials: the update kernels sum them themselves (no finish kernels)
-  const int64_t nbA = apply_partials(c);
+  const int64_t nbA = apply_partials(c, prec);
   const bool fused = !blk && nbA <= 4096 && 2 * vec_blocks(n) <= 8192;
   const bool fused_blk = blk && nbA <= 4096 && nbj <= 4096;
   double* partA = c->partials;

@@ -31,6 +31,8 @@ constexpr int kMaxVecBlocks = 2048;
 // elements), of the brick-tiled affine apply, and of the vector kernels
 int64_t element_blocks(int n, int64_t E);
 int64_t affine_tiles(int n, int nx, int ny, int nz);
+// block partials of the fused <x, A x> of the affine applies (at most affine_tiles)
+int64_t affine_partials(int n, int prec, int nx, int ny, int nz);
 int64_t vec_blocks(int64_t n);
 
 // y = A x (trans: A^T x) on affine meshes; prec: 0 f64, 1 f32, 2 bf16 in / f32 out.
@@ -45,6 +47,14 @@ hipError_t launch_apply_affine(int n, int prec, int trans, int dot, const MeshAr
 bool mfma_apply_supported(int n);
 hipError_t launch_apply_affine_mfma(int n, int dot, const MeshArgs<float>& m, const uint16_t* x, float* y,
                                     double* partials, const int* skip, hipStream_t s, int nrhs = 1);
+// the same with element planes in registers (dg_planes.hip), for the meshes
+// that use_planes names: partials only (plane_blocks of them), nrhs vectors as
+// the second grid dimension
+__host__ __device__ constexpr int plane_by(int n) { return n == 2 ? 8 : 4; }  // elements of a wave's tile along y (4 along x)
+bool use_planes(int n, int prec, int64_t E);
+int64_t plane_blocks(int n, int nx, int ny, int nz);
+hipError_t launch_apply_planes(int n, int prec, int dot, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
+                               const void* x, void* y, double* partials, const int* skip, hipStream_t s, int nrhs = 1);
 // Y = A X for nrhs vectors stored one after another (affine meshes, no fused
 // dot): the vectors are the second grid dimension of the apply kernels
 hipError_t launch_apply_affine_multi(int n, int prec, int trans, int nrhs, const MeshArgs<double>& m64,
