@@ -51,7 +51,7 @@ struct dg_ctx {
   double *z64, *s64, *w64;   // single-reduction CG
   float *r32, *d32, *p32, *q32, *z32;
   uint16_t* p16;
-  void* fb;              // trilinear meshes: lower-face line scalars between the two apply passes
+  void* fb;              // trilinear meshes: face rows between the two apply kernels (see face_rows)
   double* partials;
   CgState* st;           // [0]: outer / FP64 solve, [1]: inner solve
   int* coef_changed;     // set by dg_set_theta's exp kernel when K changed (device)
@@ -435,9 +435,9 @@ Layout layout(const dg_mesh_desc* m) {
   L.z64 = take(nd * sizeof(double));
   L.s64 = take(nd * sizeof(double));
   L.w64 = take(nd * sizeof(double));
-  L.fb = take(tri ? (size_t)E * 3 * 2 * n * n * sizeof(double) : 0);  // FP64 size, shared by the FP32 applies
+  L.fb = take(tri ? (size_t)E * 3 * 2 * n * n * sizeof(double) : 0);  // FP64 size, shared by the FP32 applies (see face_rows)
   const int64_t nb = std::max<int64_t>(std::max<int64_t>(element_blocks(n, E), vec_blocks(nd)),
-                                       affine_tiles(n, m->nx, m->ny, m->nz));
+                                       std::max<int64_t>(affine_tiles(n, m->nx, m->ny, m->nz), tri ? tri_apply_blocks(n, E) : 0));
   L.partials = take((size_t)nb * 3 * sizeof(double));
   L.st = take(2 * sizeof(CgState));
   L.flags = take(64);
@@ -459,6 +459,12 @@ void fill_scales(MeshArgs<T>& m) {
   }
 }
 
+// face_rows: the trilinear apply leaves 48 n^2 bytes per element and side in FP64
+// (half of that in FP32).  c->fb holds the lower sides in FP64 or both in FP32.
+// The upper sides in FP64 lie over z64, s64 and w64 (24 n^3 bytes per element,
+// adjacent), which only the single-reduction CG uses on these meshes (block
+// Jacobi is refused there); its applies put them over q64 and the FP32 vectors
+// (as many bytes, adjacent too), which it does not use.
 MeshArgs<double> args64(const dg_ctx* c) {
   MeshArgs<double> m;
   m.nx = c->desc.nx;
@@ -478,6 +484,7 @@ MeshArgs<double> args64(const dg_ctx* c) {
   m.vol = (1.0 / c->desc.nx) * (1.0 / c->desc.ny) * (1.0 / c->desc.nz);
   m.affg = c->affine_geom ? 1 : 0;
   m.fb = (double*)c->fb;
+  m.fbu = c->z64;
   m.go[0] = m.go[1] = m.go[2] = 0.0;
   fill_scales(m);
   return m;
@@ -501,6 +508,7 @@ MeshArgs<float> args32(const dg_ctx* c) {
   m.vol = (float)((1.0 / c->desc.nx) * (1.0 / c->desc.ny) * (1.0 / c->desc.nz));
   m.affg = c->affine_geom ? 1 : 0;
   m.fb = (float*)c->fb;
+  m.fbu = (float*)c->fb + (size_t)c->E * 6 * c->n * c->n;
   m.go[0] = m.go[1] = m.go[2] = 0.0f;
   fill_scales(m);
   return m;
@@ -527,16 +535,17 @@ MeshArgs<T> ppd_args(const dg_ctx* c, MeshArgs<T> m) {
 // dot != 0: <x, A x> into st->pq (st must then be given; par selects rho for the
 // breakdown check)
 // block partials of the fused <x, A x> of an apply: one per brick of the
-// affine and parallelepiped kernels, one per element block of the trilinear one
+// affine and parallelepiped kernels, one per block of the trilinear one
 int64_t apply_partials(const dg_ctx* c, int prec) {
-  if (c->trilinear && !c->ppd) return element_blocks(c->n, c->E);
+  if (c->trilinear && !c->ppd) return tri_apply_blocks(c->n, c->E);
   if (c->ppd) return affine_tiles(c->n, c->desc.nx, c->desc.ny, c->desc.nz);
   return affine_partials(c->n, prec, c->desc.nx, c->desc.ny, c->desc.nz);
 }
 
 hipError_t apply_any(dg_ctx* c, int prec, int trans, int dot, const void* x, void* y, CgState* st, int par,
-                     const int* skip, hipStream_t s, double* partials = nullptr) {
-  const MeshArgs<double> m64 = args64(c);
+                     const int* skip, hipStream_t s, double* partials = nullptr, double* upper_rows = nullptr) {
+  MeshArgs<double> m64 = args64(c);
+  if (upper_rows) m64.fbu = upper_rows;
   const MeshArgs<float> m32 = args32(c);
   double* part = partials ? partials : c->partials;
   if (c->ppd)  // the form is symmetric: the transpose is the same operator
@@ -1010,7 +1019,7 @@ int pcg64_single(dg_ctx* c, const dg_cg_opts* o, const double* b, double* x, int
                                                             c->partials, s)));
   HIP_TRY(c, hipMemsetAsync(c->p64, 0, n * sizeof(double), s));
   HIP_TRY(c, hipMemsetAsync(c->s64, 0, n * sizeof(double), s));
-  HIP_TRY(c, apply_any(c, DG_F64, o->transpose, 1, c->z64, c->w64, nullptr, 0, &st->done, s, partB));
+  HIP_TRY(c, apply_any(c, DG_F64, o->transpose, 1, c->z64, c->w64, nullptr, 0, &st->done, s, partB, c->q64));
   HIP_TRY(c, launch_cg2_finish(partA, nvb, partB, nbB, st, 0, s));
   CgState hs;
   int rc = read_state(c, 0, hs, s);
@@ -1020,7 +1029,7 @@ int pcg64_single(dg_ctx* c, const dg_cg_opts* o, const double* b, double* x, int
     const int chunk = std::min(check, maxit - it);
     for (int j = 0; j < chunk; ++j, ++it) {
       HIP_TRY(c, launch_cg2_update(n, x, c->r64, c->z64, c->p64, c->s64, c->w64, dinv, st, partA, s));
-      HIP_TRY(c, apply_any(c, DG_F64, o->transpose, 1, c->z64, c->w64, nullptr, 0, &st->done, s, partB));
+      HIP_TRY(c, apply_any(c, DG_F64, o->transpose, 1, c->z64, c->w64, nullptr, 0, &st->done, s, partB, c->q64));
       HIP_TRY(c, launch_cg2_finish(partA, nvb, partB, nbB, st, 1, s));
     }
     rc = read_state(c, 0, hs, s);

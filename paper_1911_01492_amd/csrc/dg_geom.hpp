@@ -10,6 +10,31 @@
 
 namespace dg {
 
+// 1 / x and sqrt(x) of normal x from the hardware approximation by Newton's
+// method (quadratic, residuals by fused multiply-add), to within an ulp and
+// without the scaling steps of the full-range functions
+__device__ __forceinline__ float recip(float x) {
+  const float r = __builtin_amdgcn_rcpf(x);
+  return fmaf(r, fmaf(-x, r, 1.0f), r);
+}
+__device__ __forceinline__ double recip(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+__device__ __forceinline__ float root(float x) {
+  const float y = __builtin_amdgcn_rsqf(x), g = x * y;
+  return fmaf(fmaf(-g, g, x), 0.5f * y, g);
+}
+__device__ __forceinline__ double root(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-g, h, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  return fma(fma(-g, g, x), h, g);
+}
+
 // J[a][d] = d x_a / d xi_d, written with the edge vectors of the corner cube:
 // dF/dxi_0 = (1-xi_1)(1-xi_2)(X1-X0) + xi_1(1-xi_2)(X3-X2) + (1-xi_1)xi_2(X5-X4) + xi_1 xi_2 (X7-X6)
 // and cyclically for the other two directions.

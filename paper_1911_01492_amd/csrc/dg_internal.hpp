@@ -117,9 +117,9 @@ struct MeshArgs {
   T go[3];              // parallelepiped meshes: the off-diagonal metric entries G_xy, G_xz,
                         // G_yz of G = |det J| J^-1 J^-T (zero on axis-parallel boxes)
   int affg;             // trilinear meshes: 1 when every element is a parallelepiped
-  T* fb;                // trilinear meshes: per element and axis d, the 2 n^2 line scalars of
-                        // its lower face (d, 0), written by the neighbour that evaluates the
-                        // face in the first pass of the apply ([(3 e + d) 2 + k] n^2 + t)
+  T *fb, *fbu;          // trilinear meshes: per element and axis d the 2 n^2 face rows of its lower
+                        // face (d, 0) in fb and of its upper face (d, 1) in fbu, left by the face
+                        // kernel for the volume kernel ([((3 e + d) 2 + k) n^2 + t])
 };
 
 // Block -> logical tile: consecutive logical tiles go to the same XCD (the

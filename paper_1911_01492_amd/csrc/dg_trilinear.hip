@@ -8,17 +8,10 @@
 //   g    = G_q gr,  G_q = w_q K |det J| J^{-1} J^{-T} = w_q K adj(J) adj(J)^T / |det J|
 //   y    = (B^T (x) B^T (x) B^T) (sum_d Dg_d^T g_d + c w_q |det J| v)
 // (the last term is the optional reaction, c = 0 without it)
-// Faces (Sec. 4.1 face form b_h^e, with its readings as in the affine path):
-// at the n^2 face Gauss points, traces and reference gradients of both sides
-// (normal derivative from each side's lines, tangential interpolation and
-// derivatives by 2D sum factorisation through LDS), physical gradients with
-// each side's own Jacobian, area-weighted normal n dS = dF/dxi_a x dF/dxi_b
-// of T^-; the test-function side is projected back with the transposed
-// tangential operators.  Each interior face is evaluated once, by its lower
-// element T^-, in the first of two passes: T^- adds its own rows and leaves
-// the two line scalars per face node of the T^+ side in a face buffer of the
-// workspace, which the second pass adds to T^+ (no atomics).  Dirichlet faces
-// are evaluated by their only element in the first pass.
+// Faces: k_tri_faces (dg_trifaces.hip) runs first and leaves every element its
+// six faces' rows in the workspace; they join the transposed contractions of
+// the volume part along the lines of their axis, so they cost no exchange of
+// their own.
 //
 // The discrete form is symmetric, so the transposed apply evaluates the same
 // kernel.
@@ -319,13 +312,26 @@ __device__ void face_term(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN*
   }
 }
 
+// The two faces normal to axis D, added to the thread's line t along D
+template <int N, int D, typename TC>
+__device__ __forceinline__ void add_faces(const MeshArgs<TC>& m, const Tables<TC>& T, int64_t e, int t, TC (&o)[N]) {
+  constexpr int NN = N * N;
+  const int64_t at = (e * 3 + D) * (2 * NN) + t;
+  const TC ol = m.fb[at], zl = m.fb[at + NN], ou = m.fbu[at], zu = m.fbu[at + NN];
+#pragma unroll
+  for (int i = 0; i < N; ++i) o[i] += T.d0[i] * zl + T.d1[i] * zu;
+  o[0] += ol;
+  o[N - 1] += ou;
+}
+
 // Volume part of the trilinear apply for the thread's element: the element
 // tile C receives (B^T (x) B^T (x) B^T)(sum_d Dg_d^T g_d + c w |det J| v) of
 // the input x (see the file header), with coefficient K (and the reaction
 // coefficients of m, if any); (ex, ey, ez): the element's grid position.
 // Xs: the element's corner slot in LDS (filled here).  All threads of the
 // block call this (it synchronises).
-template <int N, typename TC, typename TIN, bool AFF = false, int LV = 0>
+// FACES: the element's face terms, left in m.fb by k_tri_faces, join on the way.
+template <int N, typename TC, typename TIN, bool AFF = false, bool FACES = false, int LV = 0>
 __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN* __restrict__ x, int64_t e,
                            int ex, int ey, int ez, bool act, int t, int t1, int t2, TC K, TC (&Xs)[8][3], TC* A,
                            TC* B, TC* C) {
@@ -389,35 +395,41 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
     const JacZLine<TC> jz(X, T.gx[t1], T.gx[t2]);  // unused (and dropped) for AFF
 #pragma unroll
     for (int q = 0; q < N; ++q) {
-      TC Gm[3][3];
+      const TC a1 = d1[q], a2 = d2[q], a3 = d3[q];  // G gr in place of gr
       if (AFF) {
         const TC c = wq12 * T.gw[q];
         v[q] *= cw12 * T.gw[q] * dJ0;  // reaction c w |det J| u at the point
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-          for (int cc = 0; cc < 3; ++cc) Gm[r][cc] = c * G0[r][cc];
+        d1[q] = c * (G0[0][0] * a1 + G0[0][1] * a2 + G0[0][2] * a3);
+        d2[q] = c * (G0[1][0] * a1 + G0[1][1] * a2 + G0[1][2] * a3);
+        d3[q] = c * (G0[2][0] * a1 + G0[2][1] * a2 + G0[2][2] * a3);
       } else {
         TC J[3][3], Aj[3][3];
         jz.at(T.gx[q], J);
         adj3(J, Aj);
-        const TC dJ = fabs(det3(J));
-        const TC c = wq12 * T.gw[q] / dJ;
+        // det J from the adjugate's first row
+        const TC dJ = fabs(J[0][0] * Aj[0][0] + J[1][0] * Aj[0][1] + J[2][0] * Aj[0][2]);
+        const TC c = wq12 * T.gw[q] * recip(dJ);
         v[q] *= cw12 * T.gw[q] * dJ;  // reaction c w |det J| u at the point
-        // G = c adj adj^T (symmetric)
+        if constexpr (N <= 5 && sizeof(TC) == 8) {
+          // G gr with G formed: more operations, but at most 128 registers (four waves per SIMD)
+          TC Gm[3][3];
 #pragma unroll
-        for (int r = 0; r < 3; ++r)
+          for (int r = 0; r < 3; ++r)
 #pragma unroll
-          for (int cc = r; cc < 3; ++cc) {
-            const TC sgm = Aj[r][0] * Aj[cc][0] + Aj[r][1] * Aj[cc][1] + Aj[r][2] * Aj[cc][2];
-            Gm[r][cc] = c * sgm;
-            Gm[cc][r] = c * sgm;
-          }
+            for (int cc = r; cc < 3; ++cc)
+              Gm[r][cc] = Gm[cc][r] = c * (Aj[r][0] * Aj[cc][0] + Aj[r][1] * Aj[cc][1] + Aj[r][2] * Aj[cc][2]);
+          d1[q] = Gm[0][0] * a1 + Gm[0][1] * a2 + Gm[0][2] * a3;
+          d2[q] = Gm[1][0] * a1 + Gm[1][1] * a2 + Gm[1][2] * a3;
+          d3[q] = Gm[2][0] * a1 + Gm[2][1] * a2 + Gm[2][2] * a3;
+        } else {  // c adj (adj^T gr)
+          TC h[3];
+#pragma unroll
+          for (int r = 0; r < 3; ++r) h[r] = c * (Aj[0][r] * a1 + Aj[1][r] * a2 + Aj[2][r] * a3);
+          d1[q] = Aj[0][0] * h[0] + Aj[0][1] * h[1] + Aj[0][2] * h[2];
+          d2[q] = Aj[1][0] * h[0] + Aj[1][1] * h[1] + Aj[1][2] * h[2];
+          d3[q] = Aj[2][0] * h[0] + Aj[2][1] * h[1] + Aj[2][2] * h[2];
+        }
       }
-      const TC a1 = d1[q], a2 = d2[q], a3 = d3[q];  // G gr in place of gr
-      d1[q] = Gm[0][0] * a1 + Gm[0][1] * a2 + Gm[0][2] * a3;
-      d2[q] = Gm[1][0] * a1 + Gm[1][1] * a2 + Gm[1][2] * a3;
-      d3[q] = Gm[2][0] * a1 + Gm[2][1] * a2 + Gm[2][2] * a3;
     }
     contract_eo<N, TC, -1>(T.eDgt, d3, wz);
 #pragma unroll
@@ -445,6 +457,7 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
 #pragma unroll
     for (int i = 0; i < N; ++i) w[i] += r[i];
     contract_eo<N, TC, 1>(T.eBt, w, o);
+    if (FACES) add_faces<N, 0>(m, T, e, t, o);
     lds_put<N, 0, TC, LV>(A, t1, t2, o);
   }
   elem_sync<N>();
@@ -452,6 +465,7 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
     TC w[N], o[N];
     lds_get<N, 1, TC, LV>(A, t1, t2, w);
     contract_eo<N, TC, 1>(T.eBt, w, o);
+    if (FACES) add_faces<N, 1>(m, T, e, t, o);
     lds_put<N, 1, TC, LV>(A, t1, t2, o);
   }
   elem_sync<N>();
@@ -459,6 +473,7 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
     TC w[N], o[N];
     lds_get<N, 2, TC, LV>(A, t1, t2, w);
     contract_eo<N, TC, 1>(T.eBt, w, o);
+    if (FACES) add_faces<N, 2>(m, T, e, t, o);
     lds_put<N, 2, TC, LV>(C, t1, t2, o);
   }
 }
@@ -481,34 +496,28 @@ __device__ __forceinline__ void lower_line(const MeshArgs<TC>& m, const Tables<T
   lds_put<N, D>(C, t1, t2, yl);
 }
 
-// First pass of the trilinear apply: y_T = volume part + the element's three
-// upper faces (evaluated once for both of their elements; the T^+ side goes
-// to m.fb) + its lower faces on a Dirichlet boundary.  The second pass
-// (k_tri_lower) adds the lower interior faces from m.fb.
-// Waves per SIMD the first pass asks the register allocator for: three in
-// FP64 at n = 5, 6, where the face rows sharing the volume scratch tiles
-// leave LDS for three workgroups per CU (n = 6: 8% faster than with two;
-// at n = 7, 8 the registers would spill and the pass ran slower); five in
-// FP32 from n = 6 on (at most 96 VGPRs instead of 97-104; LDS leaves room
-// for five workgroups; 48^3 Q7 1-2% faster, 26^3 Q5 up to 4%)
+// Threads per block of the apply: 128 at n = 8, where the tiles of FP64 (13.8 KB
+// per element) let only two blocks of 256 reside on a CU, but five of 128
+__host__ __device__ constexpr int tri_block(int n) { return n == 8 ? 128 : kBlock; }
+
+// Waves per SIMD asked of the register allocator, as many as LDS leaves room
+// for: FP64 four up to n = 5 (at most 128 registers; 58^3 Q4 284 us with three,
+// 247 with four) and three above; FP32 five from n = 6 on.
 __host__ __device__ constexpr int tri_min_waves(int n, int bytes) {
-  return bytes == 8 && (n == 5 || n == 6) ? 3 : (bytes == 4 && n >= 6 ? 5 : 1);
+  return bytes == 8 ? (n <= 5 ? 4 : 3) : (n >= 6 ? 5 : 1);
 }
 
-template <int N, typename TIN, typename TOUT, typename TC, bool AFF>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tri_min_waves(N, sizeof(TC))))) void k_apply_trilinear(MeshArgs<TC> m, const TIN* __restrict__ x,
-                                                            TOUT* __restrict__ y, const int* skip) {
-  // FP64 at n = 4: tiles of stride 80 (no more modelled bank conflicts) hold
-  // the face rows, which then need no LDS area of their own (55.8 -> 36.9 KB
-  // per workgroup: three workgroups per CU instead of two)
-  constexpr int LV = (N == 4 && sizeof(TC) == 8) ? 2 : 0;
-  constexpr int NN = N * N, N3 = NN * N, EPB = elems_per_block(N), PE = Lay<N, TC, LV>::PE;
-  // the face rows (10 n^2 per element) live in the volume scratch tiles A, B
-  // once the volume term is done, when they fit there (n >= 5)
-  constexpr bool F_IN_AB = 10 * NN <= 2 * PE;
-  __shared__ TC sAB[2 * EPB * PE], sC[EPB * PE];
-  __shared__ TC sX[EPB][8][3], sXn[EPB][8][3];
-  __shared__ TC sFx[F_IN_AB ? 1 : EPB * 10 * NN];
+// Volume part of the apply and the face rows of k_tri_faces.  DOT: block
+// partials of <x, y> for the CG.  48^3 Q7 in FP64: 495 us, 1.6 GB (3.2 TB/s), 62 %
+// of the cycles issue vector instructions (blocks of 256: 557 us; with the
+// gradient's metric formed at every point and IEEE division 532 us).
+template <int N, typename TIN, typename TOUT, typename TC, bool AFF, bool DOT>
+__global__ __launch_bounds__(tri_block(N)) __attribute__((amdgpu_waves_per_eu(tri_min_waves(N, sizeof(TC))))) void k_apply_trilinear(
+    MeshArgs<TC> m, const TIN* __restrict__ x, TOUT* __restrict__ y, double* partials, const int* skip) {
+  constexpr int NN = N * N, N3 = NN * N, BLK = tri_block(N), EPB = BLK / NN, PE = Lay<N, TC>::PE;
+  __shared__ TC sA[EPB * PE], sB[EPB * PE], sC[EPB * PE];
+  __shared__ TC sX[EPB][8][3];
+  __shared__ double red[BLK / 64];
   if (skip != nullptr && *skip) return;
   const Tables<TC>& T = *m.tab;
   const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
@@ -516,10 +525,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tri_min_
   const int64_t e = blk * EPB + el;
   const bool act = (el < EPB) && (e < m.E);
   const int le = act ? el : 0;
-  TC* A = sAB + le * PE;
-  TC* B = sAB + (EPB + le) * PE;
-  TC* C = sC + le * PE;
-  TC(*F)[NN] = (TC(*)[NN])((F_IN_AB ? sAB : sFx) + le * 10 * NN);
   int ex = 0, ey = 0, ez = 0;
   TC K = TC(1);
   if (act) {
@@ -528,91 +533,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tri_min_
     ez = (int)(e / ((int64_t)m.nx * m.ny));
     K = m.K[e];
   }
-  tri_volume<N, TC, TIN, AFF, LV>(m, T, x, e, ex, ey, ez, act, t, t1, t2, K, sX[le], A, B, C);
-  // F_IN_AB: the face rows of an element overlap other elements' scratch tiles
-  if (F_IN_AB) __syncthreads();
-  const TC (&X)[8][3] = sX[le];
-  TC Gc[19];  // AFF: constant J, adj J, det J of the element
-  if (AFF) {
-    const TC xi[3] = {TC(0.5), TC(0.5), TC(0.5)};
-    TC J[3][3], Aj[3][3];
-    trilinear_jacobian(X, xi, J);
-    adj3(J, Aj);
-#pragma unroll
-    for (int r = 0; r < 3; ++r)
-#pragma unroll
-      for (int cc = 0; cc < 3; ++cc) {
-        Gc[3 * r + cc] = J[r][cc];
-        Gc[9 + 3 * r + cc] = Aj[r][cc];
-      }
-    Gc[18] = det3(J);
-  }
-  // upper faces for both sides; lower faces only where there is no element below
-  // (each call synchronises before touching shared buffers)
-  const bool bx0 = act && neighbour<0>(m, ex, ey, ez, 0) < 0;
-  const bool by0 = act && neighbour<1>(m, ex, ey, ez, 0) < 0;
-  const bool bz0 = act && neighbour<2>(m, ex, ey, ez, 0) < 0;
-  face_term<N, 0, TC, TIN, false, AFF, true, LV>(m, T, x, e, ex, ey, ez, X, sXn[le], K, t1, t2, C, F, act, 1, Gc);
-  face_term<N, 0, TC, TIN, false, AFF, false, LV>(m, T, x, e, ex, ey, ez, X, sXn[le], K, t1, t2, C, F, bx0, 0, Gc);
-  elem_sync<N>();
-  face_term<N, 1, TC, TIN, false, AFF, true, LV>(m, T, x, e, ex, ey, ez, X, sXn[le], K, t1, t2, C, F, act, 1, Gc);
-  face_term<N, 1, TC, TIN, false, AFF, false, LV>(m, T, x, e, ex, ey, ez, X, sXn[le], K, t1, t2, C, F, by0, 0, Gc);
-  elem_sync<N>();
-  face_term<N, 2, TC, TIN, false, AFF, true, LV>(m, T, x, e, ex, ey, ez, X, sXn[le], K, t1, t2, C, F, act, 1, Gc);
-  face_term<N, 2, TC, TIN, false, AFF, false, LV>(m, T, x, e, ex, ey, ez, X, sXn[le], K, t1, t2, C, F, bz0, 0, Gc);
-  elem_sync<N>();
-  if (act) {
-    TC o[N];
-    lds_get<N, 2, TC, LV>(C, t1, t2, o);
-    TOUT* py = y + e * N3;
-#pragma unroll
-    // y and the face buffer are not read again in this pass: nontemporal
-    // stores leave L2 to the x lines the face phases re-read
-    for (int i = 0; i < N; ++i) __builtin_nontemporal_store((TOUT)o[i], &py[lidx<N, 2>(t1, t2, i)]);
-  }
-}
-
-// Second pass: y_T += the T^+ side of each interior lower face of T, from the
-// line scalars the first pass left in m.fb (its line along d at (t1, t2):
-// l_i'(0) z added to every node, the trace term to node 0).  DOT: block
-// partials of <x, y> for the CG.
-template <int N, typename TIN, typename TOUT, typename TC, bool DOT>
-__global__ __launch_bounds__(kBlock) void k_tri_lower(MeshArgs<TC> m, const TIN* __restrict__ x,
-                                                      TOUT* __restrict__ y, double* partials, const int* skip) {
-  constexpr int NN = N * N, N3 = NN * N, EPB = elems_per_block(N), PE = Lay<N, TC>::PE;
-  __shared__ TC sC[EPB * PE];
-  __shared__ double red[kBlock / 64];
-  if (skip != nullptr && *skip) return;
-  const Tables<TC>& T = *m.tab;
-  const int64_t blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int tid = threadIdx.x, el = tid / NN, t = tid % NN, t1 = t % N, t2 = t / N;
-  const int64_t e = blk * EPB + el;
-  const bool act = (el < EPB) && (e < m.E);
-  const int le = act ? el : 0;
-  TC* C = sC + le * PE;
-  int ex = 0, ey = 0, ez = 0;
-  TOUT* py = y + e * N3;
-  if (act) {
-    ex = (int)(e % m.nx);
-    ey = (int)((e / m.nx) % m.ny);
-    ez = (int)(e / ((int64_t)m.nx * m.ny));
-    TC o[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) o[i] = (TC)py[lidx<N, 2>(t1, t2, i)];
-    lds_put<N, 2>(C, t1, t2, o);
-  }
-  elem_sync<N>();
-  if (act && neighbour<0>(m, ex, ey, ez, 0) >= 0) lower_line<N, 0>(m, T, e, t1, t2, C);
-  elem_sync<N>();
-  if (act && neighbour<1>(m, ex, ey, ez, 0) >= 0) lower_line<N, 1>(m, T, e, t1, t2, C);
-  elem_sync<N>();
-  if (act && neighbour<2>(m, ex, ey, ez, 0) >= 0) lower_line<N, 2>(m, T, e, t1, t2, C);
-  elem_sync<N>();
+  tri_volume<N, TC, TIN, AFF, true>(m, T, x, e, ex, ey, ez, act, t, t1, t2, K, sX[le], sA + le * PE, sB + le * PE,
+                                    sC + le * PE);
   double part = 0.0;
-  if (act) {
+  if (act) {  // the thread's own line: no exchange since it was written
     TC o[N], uz[N];
-    lds_get<N, 2>(C, t1, t2, o);
+    lds_get<N, 2>(sC + le * PE, t1, t2, o);
     if (DOT) glb_get<N, 2, TC, TIN>(x, e, t1, t2, uz);
+    TOUT* py = y + e * N3;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const TOUT v = (TOUT)o[i];
@@ -621,7 +549,7 @@ __global__ __launch_bounds__(kBlock) void k_tri_lower(MeshArgs<TC> m, const TIN*
     }
   }
   if (DOT) {
-    const double mine[1] = {block_sum<kBlock>(part, red)};
+    const double mine[1] = {block_sum<BLK>(part, red)};
     store_partials<1>(mine, partials, blockIdx.x);
   }
 }
@@ -951,21 +879,22 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
 }
 
 // ---------------------------------------------------------------- launchers
+int64_t tri_apply_blocks(int n, int64_t E) {
+  const int epb = tri_block(n) / (n * n);
+  return (E + epb - 1) / epb;
+}
+
 template <int N, typename TIN, typename TOUT, typename TC, bool DOT>
 static hipError_t run_tri(const MeshArgs<TC>& m, const void* x, void* y, double* partials, CgState* st, int par,
                           const int* skip, hipStream_t s) {
-  const int64_t nb = element_blocks(N, m.E);
+  const int64_t nb = tri_apply_blocks(N, m.E);
   if (m.affg)
-    hipLaunchKernelGGL((k_apply_trilinear<N, TIN, TOUT, TC, true>), dim3((unsigned)nb), dim3(kBlock), 0, s, m,
-                       (const TIN*)x, (TOUT*)y, skip);
+    hipLaunchKernelGGL((k_apply_trilinear<N, TIN, TOUT, TC, true, DOT>), dim3((unsigned)nb), dim3(tri_block(N)), 0, s, m,
+                       (const TIN*)x, (TOUT*)y, partials, skip);
   else
-    hipLaunchKernelGGL((k_apply_trilinear<N, TIN, TOUT, TC, false>), dim3((unsigned)nb), dim3(kBlock), 0, s, m,
-                       (const TIN*)x, (TOUT*)y, skip);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_tri_lower<N, TIN, TOUT, TC, DOT>), dim3((unsigned)nb), dim3(kBlock), 0, s, m, (const TIN*)x,
-                     (TOUT*)y, partials, skip);
-  e = hipGetLastError();
+    hipLaunchKernelGGL((k_apply_trilinear<N, TIN, TOUT, TC, false, DOT>), dim3((unsigned)nb), dim3(tri_block(N)), 0, s, m,
+                       (const TIN*)x, (TOUT*)y, partials, skip);
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess || !DOT || st == nullptr) return e;  // st == nullptr: partials only
   return launch_finish_dot(partials, nb, st, par, s);
 }
@@ -985,6 +914,8 @@ template <int N>
 static hipError_t run_tri_n(int prec, int dot, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
                             const void* x, void* y, double* partials, CgState* st, int par, const int* skip,
                             hipStream_t s) {
+  const hipError_t e = launch_tri_faces(N, prec, m64, m32, x, skip, s);
+  if (e != hipSuccess) return e;
   if (dot) return run_tri_prec<N, true>(prec, m64, m32, x, y, partials, st, par, skip, s);
   return run_tri_prec<N, false>(prec, m64, m32, x, y, partials, st, par, skip, s);
 }
