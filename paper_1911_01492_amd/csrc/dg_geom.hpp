@@ -114,6 +114,61 @@ __device__ __forceinline__ void face_jacobian(const T (&X)[8][3], int s, T ta, T
   }
 }
 
+template <typename TC>
+struct V3 {
+  TC x, y, z;
+};
+template <typename TC>
+__device__ __forceinline__ V3<TC> cross(const V3<TC>& a, const V3<TC>& b) {
+  return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
+}
+template <typename TC>
+__device__ __forceinline__ TC dot(const V3<TC>& a, const V3<TC>& b) {
+  return a.x * b.x + a.y * b.y + a.z * b.z;
+}
+template <typename TC>
+__device__ __forceinline__ V3<TC> lin(const V3<TC>& a, TC t, const V3<TC>& b) {
+  return {a.x + t * b.x, a.y + t * b.y, a.z + t * b.z};
+}
+template <typename TC>
+__device__ __forceinline__ V3<TC> operator-(const V3<TC>& a, const V3<TC>& b) {
+  return {a.x - b.x, a.y - b.y, a.z - b.z};
+}
+
+// Tangential axes of a face with normal axis D: B the one of smaller stride (x, or
+// y where x is the normal), A the other.
+__device__ __forceinline__ int axis_b(int D) { return D == 0 ? 1 : 0; }
+__device__ __forceinline__ int axis_a(int D) { return D == 2 ? 1 : 2; }
+
+// J of one side on the line xi_A = ta of its face xi_D = s: the column along B is
+// constant (jb, times odd), those along A and D are affine in xi_B.  odd: -1
+// where (D, A, B) is an odd permutation, so that ja x jb is the row D of adj J,
+// jb x jd the row A and odd jd x ja the row B.
+template <typename TC>
+struct FaceLine {
+  V3<TC> jb, ap, aq, dp, dq;
+  __device__ __forceinline__ FaceLine(const TC* X, int D, int s, TC ta) {
+    const int A = axis_a(D), B = axis_b(D);
+    auto corner = [&](int cd, int ca, int cb) {
+      const TC* c = X + 3 * ((cd << D) | (ca << A) | (cb << B));
+      return V3<TC>{c[0], c[1], c[2]};
+    };
+    const TC sg = s ? TC(-1) : TC(1), odd = D == 1 ? TC(1) : TC(-1);
+    auto edge = [&](const V3<TC>& p, const V3<TC>& q) {  // along D
+      return V3<TC>{sg * (q.x - p.x), sg * (q.y - p.y), sg * (q.z - p.z)};
+    };
+    const V3<TC> f00 = corner(s, 0, 0), f10 = corner(s, 1, 0), f01 = corner(s, 0, 1), f11 = corner(s, 1, 1);
+    const V3<TC> e00 = edge(f00, corner(1 - s, 0, 0)), e10 = edge(f10, corner(1 - s, 1, 0));
+    const V3<TC> e01 = edge(f01, corner(1 - s, 0, 1)), e11 = edge(f11, corner(1 - s, 1, 1));
+    const V3<TC> b0 = f01 - f00, b1 = lin(b0, ta, (f11 - f10) - b0);
+    jb = {odd * b1.x, odd * b1.y, odd * b1.z};
+    ap = f10 - f00;
+    aq = (f11 - f01) - ap;
+    dp = lin(e00, ta, e10 - e00);
+    dq = lin(e01, ta, e11 - e01) - dp;
+  }
+};
+
 template <typename T>
 __device__ __forceinline__ T det3(const T (&J)[3][3]) {
   return J[0][0] * (J[1][1] * J[2][2] - J[1][2] * J[2][1]) - J[0][1] * (J[1][0] * J[2][2] - J[1][2] * J[2][0]) +

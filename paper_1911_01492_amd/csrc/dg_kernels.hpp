@@ -109,6 +109,8 @@ hipError_t launch_dA_affine(int n, const MeshArgs<double>& m, const double* u, c
 int64_t tri_apply_blocks(int n, int64_t E);  // blocks (and block partials) of the apply
 hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const MeshArgs<float>& m32, const void* x,
                             const int* skip, hipStream_t s);
+hipError_t launch_tri_faces_dA(int n, const MeshArgs<double>& m, const double* u, const double* v, double* parts,
+                               hipStream_t s);
 hipError_t launch_apply_trilinear(int n, int prec, int trans, int dot, const MeshArgs<double>& m64,
                                   const MeshArgs<float>& m32, const void* x, void* y, double* partials,
                                   CgState* st, int par, const int* skip, hipStream_t s);

@@ -46,9 +46,7 @@ __device__ __forceinline__ int64_t neighbour(const MeshArgs<T>& m, int ex, int e
 // conflicts), n = 6 and 7 unpadded (slab strides 36 and 49, element strides
 // 216 and 343; 2% and 6% more), and n = 3 with element stride 36, so that
 // the face-scalar slot (4 n^2) fits in a tile and needs no area of its own
-// (34% more).  V = 2, n = 4 in FP64: element stride 80 (no more modelled
-// conflicts), so that two tiles hold an element's 10 n^2 face rows (the
-// trilinear apply).
+// (34% more).
 template <int N, typename TC, int V = 0>
 struct Lay {
   static constexpr bool f64 = sizeof(TC) == 8;
@@ -56,8 +54,7 @@ struct Lay {
   static constexpr int P2 = N == 6 ? (f64 ? 6 : 7) : N == 8 ? 9 : N;
   static constexpr int P3 = N == 2 ? 5 : N == 4 ? 19 : N == 6 ? (dense ? 36 : f64 ? 39 : 42) :
                             N == 7 ? (dense ? 49 : f64 ? 52 : 56) : N == 8 ? 72 : N * N;
-  static constexpr bool roomy = V == 2 && f64 && N == 4;
-  static constexpr int PE = N == 2 ? 12 : N == 3 ? (dense ? 36 : 27) : N == 4 ? (dense ? 74 : roomy ? 80 : 76) : N == 6 ? (dense ? 216 : f64 ? 244 : 252) :
+  static constexpr int PE = N == 2 ? 12 : N == 3 ? (dense ? 36 : 27) : N == 4 ? (dense ? 74 : 76) : N == 6 ? (dense ? 216 : f64 ? 244 : 252) :
                             N == 7 ? (dense ? 343 : f64 ? 369 : 401) : N == 8 ? 576 : N * N * N;
   __device__ static __forceinline__ int off(int i1, int i2, int i3) { return i1 + P2 * i2 + P3 * i3; }
 };
@@ -162,6 +159,18 @@ __device__ __forceinline__ void sym_line(const TC* Af, const EvenOdd<TC>& Ae, co
 template <int N, typename TC, bool TRANS, typename TT>
 __device__ __forceinline__ void mass_line(const TT& T, const TC (&a)[N], TC (&out)[N]) {
   sym_line<N, TC>(T.M, T.eM, a, out);
+}
+
+// out_i (+)= sum_q T_qi a_q along the line (T: one of the product tables)
+template <int N, bool ADD>
+__device__ __forceinline__ void prod_line(const double* T, const double (&a)[N], double (&out)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    double s = ADD ? out[i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < N; ++q) s += T[q * kMaxN + i] * a[q];
+    out[i] = s;
+  }
 }
 
 // Line operator with the neighbour data reduced to the two scalars the face

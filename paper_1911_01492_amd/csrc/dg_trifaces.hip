@@ -1,5 +1,6 @@
 // dg_trifaces.hip -- face terms of the trilinear apply: the first of its two
-// kernels (the second, in dg_trilinear.hip, adds them to the volume part).
+// kernels (the second, in dg_trilinear.hip, adds them to the volume part), and
+// of the sensitivity dA/dtheta.
 //
 // Every face is evaluated once, an interior one by its lower element T^-.  With
 // the trace u and the raw normal derivative g of a side on the n x n face
@@ -37,6 +38,7 @@
 #include "dg_tables.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace dg {
 
@@ -78,33 +80,7 @@ __device__ __forceinline__ double quad(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-template <typename TC>
-struct V3 {
-  TC x, y, z;
-};
-template <typename TC>
-__device__ __forceinline__ V3<TC> cross(const V3<TC>& a, const V3<TC>& b) {
-  return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
-}
-template <typename TC>
-__device__ __forceinline__ TC dot(const V3<TC>& a, const V3<TC>& b) {
-  return a.x * b.x + a.y * b.y + a.z * b.z;
-}
-template <typename TC>
-__device__ __forceinline__ V3<TC> lin(const V3<TC>& a, TC t, const V3<TC>& b) {
-  return {a.x + t * b.x, a.y + t * b.y, a.z + t * b.z};
-}
-template <typename TC>
-__device__ __forceinline__ V3<TC> operator-(const V3<TC>& a, const V3<TC>& b) {
-  return {a.x - b.x, a.y - b.y, a.z - b.z};
-}
-
-// Axes of the face: entry (r, c) of a side is node r along B and c along A, B
-// the axis of smaller stride (x, or y where x is the normal).
-__device__ __forceinline__ int axis_b(int D) { return D == 0 ? 1 : 0; }
-__device__ __forceinline__ int axis_a(int D) { return D == 2 ? 1 : 2; }
-
-// u and g of one line v
+// u and g of one line v, to a side's entry (node r along B, c along A at r RS + c)
 template <int N, typename TC, typename TT>
 __device__ __forceinline__ void put_trace(const TT& T, const TC (&v)[N], bool end, int at, TC* sU, TC* sG) {
   TC a = TC(0), b = TC(0);
@@ -221,13 +197,103 @@ __device__ __forceinline__ void load_traces_x(const TT& T, const TIN* __restrict
   }
 }
 
+// The faces of one wave: the upper faces normal to axis D of F elements, or (lower)
+// F faces of the boundary layer below, which have their upper element only.
+struct FaceSet {
+  int D, nD, stD;
+  bool lower;
+  int64_t f0, nf;  // first face, faces of this kind
+  template <int N, typename TC>
+  __device__ __forceinline__ FaceSet(const MeshArgs<TC>& m, int64_t nreg, std::integral_constant<int, N>) {
+    D = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    nD = D == 0 ? m.nx : (D == 1 ? m.ny : m.nz);
+    stD = D == 0 ? 1 : (D == 1 ? m.nx : m.nx * m.ny);
+    lower = (int64_t)blockIdx.x >= nreg;
+    f0 = (lower ? (int64_t)blockIdx.x - nreg : xcd_remap(blockIdx.x, nreg)) * faces_per_wave(N);
+    nf = lower ? m.E / nD : m.E;
+  }
+  // element and first vertex of each side (both below 2^31), by lanes below 2 F;
+  // an absent side: -1 - (the element below)
+  template <int N, typename TC>
+  __device__ __forceinline__ void sides(const MeshArgs<TC>& m, std::integral_constant<int, N>, int* el, int* vx) const {
+    const int lane = threadIdx.x & 63;
+    if (lane < 2 * faces_per_wave(N)) {
+      const unsigned nx = m.nx, ny = m.ny, q = (unsigned)min(f0 + (lane >> 1), nf - 1);
+      unsigned ex, ey, ez;
+      if (!lower) {
+        const unsigned r = q / nx;
+        ex = q - r * nx;
+        ez = r / ny;
+        ey = r - ez * ny;
+      } else {  // element q of the boundary layer
+        const unsigned n1 = D == 0 ? ny : nx, b = q / n1, a = q - b * n1;
+        ex = D == 0 ? 0 : a;
+        ey = D == 0 ? a : (D == 1 ? 0 : b);
+        ez = D == 2 ? 0 : b;
+      }
+      const int e = (int)(ex + nx * (ey + ny * ez)), c = (int)(D == 0 ? ex : (D == 1 ? ey : ez));
+      const int sv = D == 0 ? 1 : (D == 1 ? (int)nx + 1 : (int)((nx + 1) * (ny + 1)));
+      int id = e, v = (int)(ex + (nx + 1) * (ey + (ny + 1) * ez));
+      if (lane & 1) {  // the element across the upper face
+        const int d = c < nD - 1 ? 1 : 1 - nD;
+        if (lower || (c == nD - 1 && !m.periodic)) {
+          id = -1 - e;
+        } else {
+          id = e + d * stD;
+          v += d * sv;
+        }
+      }
+      el[lane] = id;
+      vx[lane] = v;
+    }
+    wave_sync();
+  }
+};
+
+// The corners of the sides, 3 corner + axis at stride 25: loaded early, stored later
+template <int N, typename TC>
+struct Corners {
+  static constexpr int SIDES = 2 * faces_per_wave(N), NC = (SIDES * 8 + 63) / 64;
+  TC cor[NC][3];
+  __device__ __forceinline__ void load(const MeshArgs<TC>& m, const int* vx) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < NC; ++r) {
+      const int q = lane + 64 * r, cc = q & 7;
+      const int v = vx[SIDES % 8 == 0 ? q >> 3 : min(q >> 3, SIDES - 1)] + (cc & 1) +
+                    (m.nx + 1) * (((cc >> 1) & 1) + (m.ny + 1) * (cc >> 2));
+      const TC* X = m.vert + (int64_t)3 * v;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) cor[r][a] = X[a];
+    }
+  }
+  __device__ __forceinline__ void store(TC* sC) const {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < NC; ++r) {
+      const int q = lane + 64 * r;
+      if (SIDES % 8 == 0 || q < SIDES * 8)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) sC[(q >> 3) * 25 + 3 * (q & 7) + a] = cor[r][a];
+    }
+  }
+};
+
 // waves per SIMD asked of the register allocator: FP64 fits 128 registers up to
 // n = 5 (at n = 3 LDS leaves room for three) and 168 above
-__host__ __device__ constexpr int face_min_waves(int n, int bytes) { return bytes == 8 ? (n <= 5 && n != 3 ? 4 : 3) : 4; }
+__host__ __device__ constexpr int face_min_waves(int n, int bytes, bool dA) {
+  if (bytes == 4) return 4;
+  return n <= (dA ? 4 : 5) && n != 3 ? 4 : (dA && (n == 6 || n == 7) ? 2 : 3);
+}
 
-template <int N, typename TIN, typename TC>
-__global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face_min_waves(N, sizeof(TC))))) void k_tri_faces(MeshArgs<TC> m, const TIN* __restrict__ x, int64_t nreg,
-                                                          const int* skip) {
+// DA: the sensitivity instead of the apply: with the coefficient G = 1/2 (1 on a
+// Dirichlet face) the rows of both sides are projected to the nodes and summed
+// against the traces of z, one value per face, into parts[7 e + 1 + 2 D + side]
+// (dg_trilinear.hip).
+template <int N, typename TIN, typename TC, bool DA>
+__global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face_min_waves(N, sizeof(TC), DA)))) void k_tri_faces(
+    MeshArgs<TC> m, const TIN* __restrict__ x, int64_t nreg, const int* skip, const TIN* __restrict__ z,
+    double* __restrict__ parts) {
   constexpr int NN = N * N, F = faces_per_wave(N), SIDES = 2 * F;
   constexpr int RS = FaceLay<N, TC>::RS, SS = FaceLay<N, TC>::SS;
   constexpr bool FULL = SIDES * N == 64;
@@ -247,77 +313,30 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
       return *(const Tables<TC>*)(ConstTab)a;
     }
   };
-  const int D = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int nD = D == 0 ? m.nx : (D == 1 ? m.ny : m.nz), stD = D == 0 ? 1 : (D == 1 ? m.nx : m.nx * m.ny);
-  // blocks below nreg: the upper faces of F elements; above: lower faces on a Dirichlet boundary
-  const bool lower = (int64_t)blockIdx.x >= nreg;
-  const int64_t f0 = (lower ? (int64_t)blockIdx.x - nreg : xcd_remap(blockIdx.x, nreg)) * F;
-  const int64_t nf = lower ? m.E / nD : m.E;
-  if (f0 >= nf) return;
+  const FaceSet fset(m, nreg, std::integral_constant<int, N>{});
+  const int D = fset.D, lane = threadIdx.x & 63;
+  const bool lower = fset.lower;
+  if (fset.f0 >= fset.nf) return;
   TC* sU = sBuf[D][0];
   TC* sG = sBuf[D][1];
   TC* sC = sCor[D];
   int* el = sEl[D];
-  if (lane < SIDES) {  // element and first vertex of each side (both below 2^31)
-    const unsigned nx = m.nx, ny = m.ny, q = (unsigned)min(f0 + (lane >> 1), nf - 1);
-    unsigned ex, ey, ez;
-    if (!lower) {
-      const unsigned r = q / nx;
-      ex = q - r * nx;
-      ez = r / ny;
-      ey = r - ez * ny;
-    } else {  // element q of the boundary layer of axis D
-      const unsigned n1 = D == 0 ? ny : nx, b = q / n1, a = q - b * n1;
-      ex = D == 0 ? 0 : a;
-      ey = D == 0 ? a : (D == 1 ? 0 : b);
-      ez = D == 2 ? 0 : b;
-    }
-    const int e = (int)(ex + nx * (ey + ny * ez)), c = (int)(D == 0 ? ex : (D == 1 ? ey : ez));
-    const int sv = D == 0 ? 1 : (D == 1 ? (int)nx + 1 : (int)((nx + 1) * (ny + 1)));
-    int id = e, v = (int)(ex + (nx + 1) * (ey + (ny + 1) * ez));
-    if (lane & 1) {  // the element across the upper face
-      const int d = c < nD - 1 ? 1 : 1 - nD;
-      if (lower || (d != 1 && !m.periodic) || (nD == 1 && !m.periodic)) {
-        id = -1 - e;
-      } else {
-        id = e + d * stD;
-        v += d * sv;
-      }
-    }
-    el[lane] = id;
-    sVx[D][lane] = v;
-  }
-  wave_sync();
-  // the corners, written to LDS after the traces
-  constexpr int NC = (SIDES * 8 + 63) / 64;
-  TC cor[NC][3];
-#pragma unroll
-  for (int r = 0; r < NC; ++r) {
-    const int q = lane + 64 * r, cc = q & 7;
-    const int v = sVx[D][SIDES % 8 == 0 ? q >> 3 : min(q >> 3, SIDES - 1)] + (cc & 1) +
-                  (m.nx + 1) * (((cc >> 1) & 1) + (m.ny + 1) * (cc >> 2));
-    const TC* X = m.vert + (int64_t)3 * v;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) cor[r][a] = X[a];
-  }
-  {
+  fset.sides(m, std::integral_constant<int, N>{}, el, sVx[D]);
+  Corners<N, TC> cor;
+  cor.load(m, sVx[D]);
+  auto traces = [&](const TIN* __restrict__ vec) {
     const auto& T = tabs();
     if (D == 0) {
-      if constexpr (TileX<N, TC>::use) load_traces_x<N, TC, TIN>(T, x, el, lower, sU, sG, sTile);
-      else load_traces<N, 0, TC, TIN>(T, x, el, lower, sU, sG);
+      if constexpr (TileX<N, TC>::use) load_traces_x<N, TC, TIN>(T, vec, el, lower, sU, sG, sTile);
+      else load_traces<N, 0, TC, TIN>(T, vec, el, lower, sU, sG);
     } else if (D == 1) {
-      load_traces<N, 1, TC, TIN>(T, x, el, lower, sU, sG);
+      load_traces<N, 1, TC, TIN>(T, vec, el, lower, sU, sG);
     } else {
-      load_traces<N, 2, TC, TIN>(T, x, el, lower, sU, sG);
+      load_traces<N, 2, TC, TIN>(T, vec, el, lower, sU, sG);
     }
-  }
-#pragma unroll
-  for (int r = 0; r < NC; ++r) {
-    const int q = lane + 64 * r;
-    if (SIDES % 8 == 0 || q < SIDES * 8)
-#pragma unroll
-      for (int a = 0; a < 3; ++a) sC[(q >> 3) * 25 + 3 * (q & 7) + a] = cor[r][a];
-  }
+  };
+  traces(x);
+  cor.store(sC);
   wave_sync();
   // ---- the lane's side and line
   const int side = lane & 1;
@@ -367,38 +386,22 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
     contract_eo<N, TC, 1>(T.eB, u, gd);
   }
   {  // ---- points (xi_A, xi_B) = (x_j, x_i), own side; J's column along B is constant, A and D affine in xi_B
-    const int A = axis_a(D), B = axis_b(D);
-    const TC odd = D == 1 ? TC(1) : TC(-1);  // (D, A, B) is an even permutation for D = 1 only
-    const TC* X = sC + sd * 25;
-    const int s = side == 0 && !lower ? 1 : 0;
-    auto corner = [&](int cd, int ca, int cb) {
-      const TC* c = X + 3 * ((cd << D) | (ca << A) | (cb << B));
-      return V3<TC>{c[0], c[1], c[2]};
-    };
     const auto& T = *m.tab;
-    const TC ta = T.gx[j], sg = s ? TC(-1) : TC(1);
-    auto edge = [&](const V3<TC>& p, const V3<TC>& q) {  // along D
-      return V3<TC>{sg * (q.x - p.x), sg * (q.y - p.y), sg * (q.z - p.z)};
-    };
-    const V3<TC> f00 = corner(s, 0, 0), f10 = corner(s, 1, 0), f01 = corner(s, 0, 1), f11 = corner(s, 1, 1);
-    const V3<TC> e00 = edge(f00, corner(1 - s, 0, 0)), e10 = edge(f10, corner(1 - s, 1, 0));
-    const V3<TC> e01 = edge(f01, corner(1 - s, 0, 1)), e11 = edge(f11, corner(1 - s, 1, 1));
-    const V3<TC> b0 = f01 - f00, b1 = lin(b0, ta, (f11 - f10) - b0), jb = {odd * b1.x, odd * b1.y, odd * b1.z};
-    const V3<TC> ap = f10 - f00, aq = (f11 - f01) - ap;
-    const V3<TC> dp = lin(e00, ta, e10 - e00), dq = lin(e01, ta, e11 - e01) - dp;
+    const FaceLine<TC> L(sC + sd * 25, D, side == 0 && !lower ? 1 : 0, T.gx[j]);
+    const TC odd = D == 1 ? TC(1) : TC(-1);
     const bool has = el[2 * f + 1] >= 0;
-    const TC G = m.G[(int64_t)6 * el[2 * f] + 2 * D + (lower ? 0 : 1)];
+    const TC G = DA ? (has ? TC(0.5) : TC(1)) : m.G[(int64_t)6 * el[2 * f] + 2 * D + (lower ? 0 : 1)];
     const TC pen = (D == 0 ? m.sg[0] : (D == 1 ? m.sg[1] : m.sg[2])) * G * (has ? TC(2) : TC(1));
     const TC gs = side != 0 || lower ? -G : G;  // sign of J on this side, outward N on a lower boundary
     const TC wj = T.gw[j];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const TC tb = T.gx[i], w = wj * T.gw[i];
-      const V3<TC> ja = lin(ap, tb, aq), jd = lin(dp, tb, dq);
-      const V3<TC> nd = cross(ja, jb);
+      const V3<TC> ja = lin(L.ap, tb, L.aq), jd = lin(L.dp, tb, L.dq);
+      const V3<TC> nd = cross(ja, L.jb);
       const V3<TC> Nv = {quad<0xA0>(nd.x), quad<0xA0>(nd.y), quad<0xA0>(nd.z)};
       const TC idet = recip(dot(jd, nd));
-      const TC cd = dot(nd, Nv), ca = dot(cross(jb, jd), Nv), cb = dot(cross(jd, ja), Nv);
+      const TC cd = dot(nd, Nv), ca = dot(cross(L.jb, jd), Nv), cb = dot(cross(jd, ja), Nv);
       TC fl = (cd * gd[i] + ca * ga[i] + odd * (cb * gb[i])) * idet;
       fl += quad<0xB1>(fl);
       const TC Jm = v[i] - quad<0xB1>(v[i]);
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
     const TC odd = D == 1 ? TC(1) : TC(-1);
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] += odd * u[i];
-    if (D >= 1) {
+    if (DA || D >= 1) {
       contract_eo<N, TC, 1>(T.eBt, v, u);
       contract_eo<N, TC, 1>(T.eBt, ga, g);
       contract_eo<N, TC, 1>(T.eBt, gd, gb);
@@ -458,7 +461,7 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
     contract_eo<N, TC, -1>(T.eDgt, ga, u);
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] += u[i];
-    if (D == 2) {
+    if (DA || D == 2) {
       contract_eo<N, TC, 1>(T.eBt, v, u);
       contract_eo<N, TC, 1>(T.eBt, gd, g);
 #pragma unroll
@@ -468,7 +471,24 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
       }
     }
     const int e = el[sd2];
-    if (on && e >= 0 && f0 + (sd2 >> 1) < nf) {
+    const bool own = on && e >= 0 && fset.f0 + (sd2 >> 1) < fset.nf;
+    if constexpr (DA) {
+      // the rows against the traces of z, summed per face in lane order
+      wave_sync();
+      traces(z);
+      wave_sync();
+      TC p = TC(0);
+#pragma unroll
+      for (int i = 0; i < N; ++i) p += v[i] * sU[row2 + i] + gd[i] * sG[row2 + i];
+      wave_sync();
+      if (on) sU[lane] = own ? p : TC(0);
+      wave_sync();
+      if (lane < F && fset.f0 + lane < fset.nf) {
+        TC t = TC(0);
+        for (int i = 0; i < 2 * N; ++i) t += sU[lane * 2 * N + i];
+        parts[(int64_t)7 * el[2 * lane] + 1 + 2 * D + (lower ? 0 : 1)] = t;
+      }
+    } else if (own) {
       TC* fb = ((sd2 & 1) != 0 || lower ? m.fb : m.fbu) + ((int64_t)e * 3 + D) * (2 * NN) + j2;
 #pragma unroll
       for (int i = 0; i < N; ++i) fb[i * N] = v[i];
@@ -478,23 +498,41 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
   }
 }
 
+// blocks: F elements' upper faces each, then the boundary layers (the axis with
+// most of them sets their number)
+template <int N>
+static unsigned face_blocks(const MeshArgs<double>& m, int64_t& nreg) {
+  const int64_t F = faces_per_wave(N), most = m.periodic ? 0 : m.E / std::min(m.nx, std::min(m.ny, m.nz));
+  nreg = (m.E + F - 1) / F;
+  return (unsigned)(nreg + (most + F - 1) / F);
+}
 template <int N>
 static hipError_t run_tri_faces(int prec, const MeshArgs<double>& m64, const MeshArgs<float>& m32, const void* x,
                                 const int* skip, hipStream_t s) {
-  const int64_t F = faces_per_wave(N), nreg = (m64.E + F - 1) / F;
-  // boundary faces: the axis with most of them sets the blocks
-  const int64_t most = m64.periodic ? 0 : m64.E / std::min(m64.nx, std::min(m64.ny, m64.nz));
-  const dim3 grid((unsigned)(nreg + (most + F - 1) / F)), block(kFaceBlock);
+  int64_t nreg;
+  const dim3 grid(face_blocks<N>(m64, nreg)), block(kFaceBlock);
   switch (prec) {
     case 0:
-      hipLaunchKernelGGL((k_tri_faces<N, double, double>), grid, block, 0, s, m64, (const double*)x, nreg, skip);
+      hipLaunchKernelGGL((k_tri_faces<N, double, double, false>), grid, block, 0, s, m64, (const double*)x, nreg, skip,
+                         (const double*)nullptr, (double*)nullptr);
       break;
-    case 1: hipLaunchKernelGGL((k_tri_faces<N, float, float>), grid, block, 0, s, m32, (const float*)x, nreg, skip); break;
+    case 1: hipLaunchKernelGGL((k_tri_faces<N, float, float, false>), grid, block, 0, s, m32, (const float*)x, nreg, skip,
+                         (const float*)nullptr, (double*)nullptr); break;
     case 2:
-      hipLaunchKernelGGL((k_tri_faces<N, uint16_t, float>), grid, block, 0, s, m32, (const uint16_t*)x, nreg, skip);
+      hipLaunchKernelGGL((k_tri_faces<N, uint16_t, float, false>), grid, block, 0, s, m32, (const uint16_t*)x, nreg, skip,
+                         (const uint16_t*)nullptr, (double*)nullptr);
       break;
     default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
+}
+template <int N>
+static hipError_t run_tri_faces_dA(const MeshArgs<double>& m, const double* u, const double* v, double* parts,
+                                   hipStream_t s) {
+  int64_t nreg;
+  const dim3 grid(face_blocks<N>(m, nreg)), block(kFaceBlock);
+  hipLaunchKernelGGL((k_tri_faces<N, double, double, true>), grid, block, 0, s, m, v, nreg, (const int*)nullptr, u,
+                     parts);
   return hipGetLastError();
 }
 hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const MeshArgs<float>& m32, const void* x,
@@ -507,6 +545,19 @@ hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const 
     case 6: return run_tri_faces<6>(prec, m64, m32, x, skip, s);
     case 7: return run_tri_faces<7>(prec, m64, m32, x, skip, s);
     case 8: return run_tri_faces<8>(prec, m64, m32, x, skip, s);
+  }
+  return hipErrorInvalidValue;
+}
+hipError_t launch_tri_faces_dA(int n, const MeshArgs<double>& m, const double* u, const double* v, double* parts,
+                               hipStream_t s) {
+  switch (n) {
+    case 2: return run_tri_faces_dA<2>(m, u, v, parts, s);
+    case 3: return run_tri_faces_dA<3>(m, u, v, parts, s);
+    case 4: return run_tri_faces_dA<4>(m, u, v, parts, s);
+    case 5: return run_tri_faces_dA<5>(m, u, v, parts, s);
+    case 6: return run_tri_faces_dA<6>(m, u, v, parts, s);
+    case 7: return run_tri_faces_dA<7>(m, u, v, parts, s);
+    case 8: return run_tri_faces_dA<8>(m, u, v, parts, s);
   }
   return hipErrorInvalidValue;
 }

@@ -49,269 +49,6 @@ __device__ __forceinline__ void corner_at(const MeshArgs<TC>& m, int cx, int cy,
   out = m.vert[3 * v + a];
 }
 
-// Face contributions of the face normal to axis D on side s of the thread's
-// element, added into the element's accumulator tile Y.  UNIT: with the face
-// coefficient set to 1 (gamma_e on interior faces, K_T on boundary faces),
-// for the sensitivity dA/dtheta.  AFF: the element is a parallelepiped and
-// Gc holds its constant J, adj J and det J.  PAIR (upper faces, s = 1): the
-// face is evaluated once for both elements; the neighbour's side (T^+, whose
-// lower face it is) is projected as well and its two line scalars per face
-// node go to m.fb for the second pass.  All threads of the block call this
-// (it synchronises); act marks threads owning an element.
-template <int N, int D, typename TC, typename TIN, bool UNIT = false, bool AFF = false, bool PAIR = false, int LV = 0>
-__device__ void face_term(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN* __restrict__ x, int64_t e,
-                          int ex, int ey, int ez, const TC (&X)[8][3], TC (&Xn)[8][3], TC K, int t1, int t2,
-                          TC* Y, TC (*F)[N * N], bool act, int s, const TC* Gc = nullptr) {
-  constexpr int NN = N * N;
-  const int t = t1 + N * t2;
-  const int ax = (D == 0) ? 1 : 0;  // reference axis of t1
-  const int bx = (D == 2) ? 1 : 2;  // reference axis of t2
-  const TC* dS = s ? T.d1 : T.d0;   // own derivative at the own face end
-  const TC* dN = s ? T.d0 : T.d1;   // neighbour's derivative at its face end
-  int64_t nb = -1;
-  TC Uo = TC(0), Go = TC(0), Un = TC(0), Gn = TC(0);
-  if (act) {
-    nb = neighbour<D>(m, ex, ey, ez, s);
-    // the neighbour's corners, staged once per element (read after the barriers below)
-    if (nb >= 0) {
-      int g[3] = {ex, ey, ez};
-      g[D] = nb_coord(g[D], s, D == 0 ? m.nx : (D == 1 ? m.ny : m.nz), m.periodic);
-      for (int q = t; q < 24; q += NN) corner_at(m, g[0], g[1], g[2], q / 3, q % 3, Xn[q / 3][q % 3]);
-    }
-    TC own[N];
-    glb_get<N, D, TC, TIN>(x, e, t1, t2, own);
-    Uo = own[s ? N - 1 : 0];
-#pragma unroll
-    for (int i = 0; i < N; ++i) Go += dS[i] * own[i];
-    if (nb >= 0) {
-      TC nl[N];
-      glb_get<N, D, TC, TIN>(x, nb, t1, t2, nl);
-      Un = nl[s ? 0 : N - 1];
-#pragma unroll
-      for (int i = 0; i < N; ++i) Gn += dN[i] * nl[i];
-    }
-  }
-  elem_sync<N>();  // face buffers free
-  if (act) {
-    F[0][t] = Uo;
-    F[1][t] = Go;
-    F[2][t] = Un;
-    F[3][t] = Gn;
-  }
-  elem_sync<N>();
-  if (act) {  // interpolation / derivative along t1 (axis ax)
-    TC bu = 0, du = 0, bg = 0, bun = 0, dun = 0, bgn = 0;
-#pragma unroll
-    for (int a = 0; a < N; ++a) {
-      const TC B = T.B[t1 * kMaxN + a], Dd = T.D[t1 * kMaxN + a];
-      bu += B * F[0][t2 * N + a];
-      du += Dd * F[0][t2 * N + a];
-      bg += B * F[1][t2 * N + a];
-      bun += B * F[2][t2 * N + a];
-      dun += Dd * F[2][t2 * N + a];
-      bgn += B * F[3][t2 * N + a];
-    }
-    F[4][t] = bu;
-    F[5][t] = du;
-    F[6][t] = bg;
-    F[7][t] = bun;
-    F[8][t] = dun;
-    F[9][t] = bgn;
-  }
-  elem_sync<N>();
-  TC P = 0, Ra = 0, Rb = 0, Rd = 0;
-  TC Pn = 0, Ran = 0, Rbn = 0, Rdn = 0;  // PAIR: the neighbour's side (T^+)
-  if (act) {  // along t2 (axis bx): values at face Gauss point (qa, qb) = (t1, t2)
-    TC uo = 0, gao = 0, gbo = 0, gdo = 0, un = 0, gan = 0, gbn = 0, gdn = 0;
-#pragma unroll
-    for (int b = 0; b < N; ++b) {
-      const TC B = T.B[t2 * kMaxN + b], Dd = T.D[t2 * kMaxN + b];
-      uo += B * F[4][b * N + t1];
-      gao += B * F[5][b * N + t1];
-      gbo += Dd * F[4][b * N + t1];
-      gdo += B * F[6][b * N + t1];
-      un += B * F[7][b * N + t1];
-      gan += B * F[8][b * N + t1];
-      gbn += Dd * F[7][b * N + t1];
-      gdn += B * F[9][b * N + t1];
-    }
-    TC xi[3];
-    xi[D] = TC(s);
-    xi[ax] = T.gx[t1];
-    xi[bx] = T.gx[t2];
-    TC Jo[3][3], Ao[3][3], deto;
-    if (AFF) {  // parallelepiped: the element's constant J, adj J, det J (Gc = 9 + 9 + 1 values)
-#pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int cc = 0; cc < 3; ++cc) {
-          Jo[r][cc] = Gc[3 * r + cc];
-          Ao[r][cc] = Gc[9 + 3 * r + cc];
-        }
-      deto = Gc[18];
-    } else {
-      face_jacobian<D>(X, s, xi[ax], xi[bx], Jo);
-      adj3(Jo, Ao);
-      deto = det3(Jo);
-    }
-    TC gro[3];
-    gro[D] = gdo;
-    gro[ax] = gao;
-    gro[bx] = gbo;
-    const TC ideto = TC(1) / deto;
-    TC go[3];  // physical gradient, own side: adj^T gr / det
-#pragma unroll
-    for (int c = 0; c < 3; ++c) go[c] = (Ao[0][c] * gro[0] + Ao[1][c] * gro[1] + Ao[2][c] * gro[2]) * ideto;
-    const TC w = T.gw[t1] * T.gw[t2];
-    const TC h = D == 0 ? m.hx : (D == 1 ? m.hy : m.hz);
-    const TC sig = m.sig_hat / h;
-    TC Nv[3];
-    const int c1 = (D + 1) % 3, c2 = (D + 2) % 3;
-    if (nb >= 0) {
-      TC xin[3];
-      xin[D] = TC(1 - s);
-      xin[ax] = xi[ax];
-      xin[bx] = xi[bx];
-      TC Jn[3][3], An[3][3];
-      if (AFF) {  // the neighbour is a parallelepiped too: J is its three edge vectors
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-          for (int cc = 0; cc < 3; ++cc) Jn[r][cc] = Xn[1 << cc][r] - Xn[0][r];
-      } else {
-        face_jacobian<D>(Xn, 1 - s, xi[ax], xi[bx], Jn);
-      }
-      adj3(Jn, An);
-      const TC idetn = TC(1) / det3(Jn);
-      TC grn[3];
-      grn[D] = gdn;
-      grn[ax] = gan;
-      grn[bx] = gbn;
-      TC gn[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) gn[c] = (An[0][c] * grn[0] + An[1][c] * grn[1] + An[2][c] * grn[2]) * idetn;
-      // n dS from T^-: the own element on the upper face, the neighbour on the lower face
-      const TC (&Jm)[3][3] = s ? Jo : Jn;
-      Nv[0] = Jm[1][c1] * Jm[2][c2] - Jm[2][c1] * Jm[1][c2];
-      Nv[1] = Jm[2][c1] * Jm[0][c2] - Jm[0][c1] * Jm[2][c2];
-      Nv[2] = Jm[0][c1] * Jm[1][c2] - Jm[1][c1] * Jm[0][c2];
-      const TC area = sqrt(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
-      const TC Kn = m.K[nb];
-      const TC gam = UNIT ? TC(1) : TC(2) * K * Kn / (K + Kn);
-      const TC Jq = s ? uo - un : un - uo;
-      const TC Fq = TC(0.5) * gam * w * ((go[0] + gn[0]) * Nv[0] + (go[1] + gn[1]) * Nv[1] + (go[2] + gn[2]) * Nv[2]);
-      const TC pen = sig * gam * area * w * Jq;
-      P = s ? (pen - Fq) : (Fq - pen);
-      const TC cr = -TC(0.5) * gam * w * Jq * ideto;
-      TC R[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) R[c] = cr * (Ao[c][0] * Nv[0] + Ao[c][1] * Nv[1] + Ao[c][2] * Nv[2]);
-      Ra = R[ax];
-      Rb = R[bx];
-      Rd = R[D];
-      if (PAIR) {  // T^+ side of the same face: the opposite flux-minus-penalty term, and
-                   // its symmetry term with its own adj J and det J
-        Pn = -P;
-        const TC crn = -TC(0.5) * gam * w * Jq * idetn;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) R[c] = crn * (An[c][0] * Nv[0] + An[c][1] * Nv[1] + An[c][2] * Nv[2]);
-        Ran = R[ax];
-        Rbn = R[bx];
-        Rdn = R[D];
-      }
-    } else {
-      // weak Dirichlet: -K grad u.n v - K grad v.n u + sigma K u v, outward n
-      const TC sg = s ? TC(1) : TC(-1);
-      Nv[0] = sg * (Jo[1][c1] * Jo[2][c2] - Jo[2][c1] * Jo[1][c2]);
-      Nv[1] = sg * (Jo[2][c1] * Jo[0][c2] - Jo[0][c1] * Jo[2][c2]);
-      Nv[2] = sg * (Jo[0][c1] * Jo[1][c2] - Jo[1][c1] * Jo[0][c2]);
-      const TC area = sqrt(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
-      const TC Kb = UNIT ? TC(1) : K;
-      P = -Kb * w * (go[0] * Nv[0] + go[1] * Nv[1] + go[2] * Nv[2]) + sig * Kb * area * w * uo;
-      const TC cr = -Kb * w * uo * ideto;
-      TC R[3];
-#pragma unroll
-      for (int c = 0; c < 3; ++c) R[c] = cr * (Ao[c][0] * Nv[0] + Ao[c][1] * Nv[1] + Ao[c][2] * Nv[2]);
-      Ra = R[ax];
-      Rb = R[bx];
-      Rd = R[D];
-    }
-    F[0][t] = P;  // F[0..3] were last read before the previous barrier
-    F[1][t] = Ra;
-    F[2][t] = Rb;
-    F[3][t] = Rd;
-  }
-  if (PAIR) {
-    // F[4..9] are read above by every thread of the element, which may span
-    // two wavefronts (n^2 not dividing 64): the T^+ rows wait for all of them
-    elem_sync<N>();
-    if (act) {
-      F[4][t] = Pn;
-      F[5][t] = Ran;
-      F[6][t] = Rbn;
-      F[7][t] = Rdn;
-    }
-  }
-  elem_sync<N>();
-  // transposed tangential operators, contraction over qb: thread (qa, b) = (t1, t2);
-  // rows: own side F[4..6] (PAIR: F[0..2]), neighbour side F[3..5]
-  constexpr int O = PAIR ? 0 : 4;
-  {
-    TC xs = 0, ys = 0, zs = 0, xn = 0, yn = 0, zn = 0;
-    if (act) {
-#pragma unroll
-      for (int qb = 0; qb < N; ++qb) {
-        const TC B = T.B[qb * kMaxN + t2], Dd = T.D[qb * kMaxN + t2];
-        xs += B * F[0][qb * N + t1] + Dd * F[2][qb * N + t1];
-        ys += B * F[1][qb * N + t1];
-        zs += B * F[3][qb * N + t1];
-        if (PAIR) {
-          xn += B * F[4][qb * N + t1] + Dd * F[6][qb * N + t1];
-          yn += B * F[5][qb * N + t1];
-          zn += B * F[7][qb * N + t1];
-        }
-      }
-    }
-    if (PAIR) elem_sync<N>();  // the inputs are overwritten below
-    if (act) {
-      F[O + 0][t2 * N + t1] = xs;
-      F[O + 1][t2 * N + t1] = ys;
-      F[O + 2][t2 * N + t1] = zs;
-      if (PAIR) {
-        F[3][t2 * N + t1] = xn;
-        F[4][t2 * N + t1] = yn;
-        F[5][t2 * N + t1] = zn;
-      }
-    }
-  }
-  elem_sync<N>();
-  if (act) {  // contraction over qa: thread (a, b) = (t1, t2) owns face node (a, b) of its line
-    TC out = 0, z = 0, outn = 0, zn = 0;
-#pragma unroll
-    for (int qa = 0; qa < N; ++qa) {
-      const TC B = T.B[qa * kMaxN + t1], Dd = T.D[qa * kMaxN + t1];
-      out += B * F[O + 0][t2 * N + qa] + Dd * F[O + 1][t2 * N + qa];
-      z += B * F[O + 2][t2 * N + qa];
-      if (PAIR) {
-        outn += B * F[3][t2 * N + qa] + Dd * F[4][t2 * N + qa];
-        zn += B * F[5][t2 * N + qa];
-      }
-    }
-    TC yl[N];
-    lds_get<N, D, TC, LV>(Y, t1, t2, yl);
-#pragma unroll
-    for (int i = 0; i < N; ++i) yl[i] += dS[i] * z;
-    yl[s ? N - 1 : 0] += out;
-    lds_put<N, D, TC, LV>(Y, t1, t2, yl);
-    if (PAIR && nb >= 0) {  // the neighbour's line (t1, t2) along D, added by its second pass
-      TC* fbn = m.fb + ((int64_t)nb * 3 + D) * 2 * NN;
-      // read once, by the second pass: stored nontemporal
-      __builtin_nontemporal_store(outn, &fbn[t]);
-      __builtin_nontemporal_store(zn, &fbn[NN + t]);
-    }
-  }
-}
-
 // The two faces normal to axis D, added to the thread's line t along D
 template <int N, int D, typename TC>
 __device__ __forceinline__ void add_faces(const MeshArgs<TC>& m, const Tables<TC>& T, int64_t e, int t, TC (&o)[N]) {
@@ -331,7 +68,7 @@ __device__ __forceinline__ void add_faces(const MeshArgs<TC>& m, const Tables<TC
 // Xs: the element's corner slot in LDS (filled here).  All threads of the
 // block call this (it synchronises).
 // FACES: the element's face terms, left in m.fb by k_tri_faces, join on the way.
-template <int N, typename TC, typename TIN, bool AFF = false, bool FACES = false, int LV = 0>
+template <int N, typename TC, typename TIN, bool AFF = false, bool FACES = false>
 __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN* __restrict__ x, int64_t e,
                            int ex, int ey, int ez, bool act, int t, int t1, int t2, TC K, TC (&Xs)[8][3], TC* A,
                            TC* B, TC* C) {
@@ -342,39 +79,39 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
     glb_get<N, 2, TC, TIN>(x, e, t1, t2, uz);
     TC a[N];
     contract_eo<N, TC, 1>(T.eB, uz, a);  // phase Z: interpolate along z
-    lds_put<N, 2, TC, LV>(A, t1, t2, a);
+    lds_put<N, 2>(A, t1, t2, a);
   }
   elem_sync<N>();
   const TC (&X)[8][3] = Xs;
   if (act) {  // phase Y
     TC a[N], b[N];
-    lds_get<N, 1, TC, LV>(A, t1, t2, a);
+    lds_get<N, 1>(A, t1, t2, a);
     contract_eo<N, TC, 1>(T.eB, a, b);
-    lds_put<N, 1, TC, LV>(B, t1, t2, b);
+    lds_put<N, 1>(B, t1, t2, b);
   }
   elem_sync<N>();
   if (act) {  // phase X: v and d/dxi_0
     TC a[N], v[N], d1[N];
-    lds_get<N, 0, TC, LV>(B, t1, t2, a);
+    lds_get<N, 0>(B, t1, t2, a);
     contract_eo<N, TC, 1>(T.eB, a, v);
     contract_eo<N, TC, -1>(T.eDg, v, d1);
-    lds_put<N, 0, TC, LV>(A, t1, t2, v);
-    lds_put<N, 0, TC, LV>(C, t1, t2, d1);
+    lds_put<N, 0>(A, t1, t2, v);
+    lds_put<N, 0>(C, t1, t2, d1);
   }
   elem_sync<N>();
   if (act) {  // phase Y': d/dxi_1
     TC v[N], d2[N];
-    lds_get<N, 1, TC, LV>(A, t1, t2, v);
+    lds_get<N, 1>(A, t1, t2, v);
     contract_eo<N, TC, -1>(T.eDg, v, d2);
-    lds_put<N, 1, TC, LV>(B, t1, t2, d2);
+    lds_put<N, 1>(B, t1, t2, d2);
   }
   elem_sync<N>();
   if (act) {  // phase Z': d/dxi_2, geometry, g = G gr, Dg_z^T g_2
     TC d1[N], d2[N], d3[N], wz[N], v[N];
-    lds_get<N, 2, TC, LV>(A, t1, t2, v);
+    lds_get<N, 2>(A, t1, t2, v);
     contract_eo<N, TC, -1>(T.eDg, v, d3);
-    lds_get<N, 2, TC, LV>(C, t1, t2, d1);
-    lds_get<N, 2, TC, LV>(B, t1, t2, d2);
+    lds_get<N, 2>(C, t1, t2, d1);
+    lds_get<N, 2>(B, t1, t2, d2);
     const TC wq12 = T.gw[t1] * T.gw[t2] * K;
     const TC cw12 = m.R ? m.R[e] * T.gw[t1] * T.gw[t2] : TC(0);  // reaction weight
     TC G0[3][3], dJ0 = TC(1);
@@ -434,47 +171,47 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
     contract_eo<N, TC, -1>(T.eDgt, d3, wz);
 #pragma unroll
     for (int q = 0; q < N; ++q) wz[q] += v[q];
-    lds_put<N, 2, TC, LV>(A, t1, t2, wz);
-    lds_put<N, 2, TC, LV>(C, t1, t2, d1);
-    lds_put<N, 2, TC, LV>(B, t1, t2, d2);
+    lds_put<N, 2>(A, t1, t2, wz);
+    lds_put<N, 2>(C, t1, t2, d1);
+    lds_put<N, 2>(B, t1, t2, d2);
   }
   elem_sync<N>();
   if (act) {  // phase Y'': += Dg_y^T g_1
     TC g2[N], w[N], r[N];
-    lds_get<N, 1, TC, LV>(B, t1, t2, g2);
-    lds_get<N, 1, TC, LV>(A, t1, t2, w);
+    lds_get<N, 1>(B, t1, t2, g2);
+    lds_get<N, 1>(A, t1, t2, w);
     contract_eo<N, TC, -1>(T.eDgt, g2, r);
 #pragma unroll
     for (int i = 0; i < N; ++i) w[i] += r[i];
-    lds_put<N, 1, TC, LV>(A, t1, t2, w);
+    lds_put<N, 1>(A, t1, t2, w);
   }
   elem_sync<N>();
   if (act) {  // phase X'': += Dg_x^T g_0, then B_x^T
     TC g1[N], w[N], r[N], o[N];
-    lds_get<N, 0, TC, LV>(C, t1, t2, g1);
-    lds_get<N, 0, TC, LV>(A, t1, t2, w);
+    lds_get<N, 0>(C, t1, t2, g1);
+    lds_get<N, 0>(A, t1, t2, w);
     contract_eo<N, TC, -1>(T.eDgt, g1, r);
 #pragma unroll
     for (int i = 0; i < N; ++i) w[i] += r[i];
     contract_eo<N, TC, 1>(T.eBt, w, o);
     if (FACES) add_faces<N, 0>(m, T, e, t, o);
-    lds_put<N, 0, TC, LV>(A, t1, t2, o);
+    lds_put<N, 0>(A, t1, t2, o);
   }
   elem_sync<N>();
   if (act) {  // phase Y''': B_y^T
     TC w[N], o[N];
-    lds_get<N, 1, TC, LV>(A, t1, t2, w);
+    lds_get<N, 1>(A, t1, t2, w);
     contract_eo<N, TC, 1>(T.eBt, w, o);
     if (FACES) add_faces<N, 1>(m, T, e, t, o);
-    lds_put<N, 1, TC, LV>(A, t1, t2, o);
+    lds_put<N, 1>(A, t1, t2, o);
   }
   elem_sync<N>();
   if (act) {  // phase Z''': B_z^T -> accumulator C
     TC w[N], o[N];
-    lds_get<N, 2, TC, LV>(A, t1, t2, w);
+    lds_get<N, 2>(A, t1, t2, w);
     contract_eo<N, TC, 1>(T.eBt, w, o);
     if (FACES) add_faces<N, 2>(m, T, e, t, o);
-    lds_put<N, 2, TC, LV>(C, t1, t2, o);
+    lds_put<N, 2>(C, t1, t2, o);
   }
 }
 
@@ -556,25 +293,24 @@ __global__ __launch_bounds__(tri_block(N)) __attribute__((amdgpu_waves_per_eu(tr
 
 // ---------------------------------------------------------------- dA / dtheta
 // Per element T, with u and v: parts[7 T] = u_T . (volume form of T with
-// K = 1) v_T and parts[7 T + 1 + 2 d + s] = u_T . (rows of T of the face form
-// of face (d, s) with unit coefficient) v.  The reaction term does not depend
-// on theta and is left out.
+// K = 1) v_T here, and from k_tri_faces the whole form of a face with unit
+// coefficient, u . (rows of both sides) v: parts[7 T + 2 + 2 d] of the upper
+// face (d, 1), parts[7 T + 1 + 2 d] of a lower face on a Dirichlet boundary.
+// The reaction term does not depend on theta and is left out.
+// 23 x 18 x 21 Q4: 13 us here and 25 us for the faces; 85 us with every face
+// evaluated from both of its elements, by points, in one kernel.
 template <int N>
 __global__ __launch_bounds__(kBlock) void k_dA_parts_trilinear(MeshArgs<double> m, const double* __restrict__ u,
                                                                const double* __restrict__ v,
                                                                double* __restrict__ parts) {
   constexpr int NN = N * N, EPB = elems_per_block(N), PE = Lay<N, double>::PE;
   __shared__ double sA[EPB * PE], sB[EPB * PE], sC[EPB * PE];
-  __shared__ double sX[EPB][8][3], sXn[EPB][8][3];
-  __shared__ double sF[EPB][10][NN];
-  __shared__ double sRed[kBlock];
+  __shared__ double sX[EPB][8][3];
   const Tables<double>& T = *m.tab;
   const int tid = threadIdx.x, el = tid / NN, t = tid % NN, t1 = t % N, t2 = t / N;
   const int64_t e = (int64_t)blockIdx.x * EPB + el;
   const bool act = (el < EPB) && (e < m.E);
   const int le = act ? el : 0;
-  double* A = sA + le * PE;
-  double* B = sB + le * PE;
   double* C = sC + le * PE;
   int ex = 0, ey = 0, ez = 0;
   if (act) {
@@ -584,51 +320,28 @@ __global__ __launch_bounds__(kBlock) void k_dA_parts_trilinear(MeshArgs<double> 
   }
   MeshArgs<double> m1 = m;
   m1.R = nullptr;
-  tri_volume<N, double, double>(m1, T, v, e, ex, ey, ez, act, t, t1, t2, 1.0, sX[le], A, B, C);
-  const double (&X)[8][3] = sX[le];
-  double uz[N];
-  if (act) glb_get<N, 2, double, double>(u, e, t1, t2, uz);
-  // u_T . C for the thread's element, then C = 0 (deterministic: per-thread
-  // partial sums, added in thread order by the element's first thread)
-  auto take = [&](int slot) {
-    elem_sync<N>();
-    double p = 0.0;
-    if (act) {
-      double c[N], z[N];
-      lds_get<N, 2>(C, t1, t2, c);
+  tri_volume<N, double, double>(m1, T, v, e, ex, ey, ez, act, t, t1, t2, 1.0, sX[le], sA + le * PE, sB + le * PE, C);
+  // u_T . C: the lines' sums, added in thread order by the element's first thread
+  double* sRed = sB + le * PE;  // no longer read (act) by the volume part's last phase
+  if (act) {
+    double uz[N], c[N], p = 0.0;
+    glb_get<N, 2, double, double>(u, e, t1, t2, uz);
+    lds_get<N, 2>(C, t1, t2, c);
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        p += uz[i] * c[i];
-        z[i] = 0.0;
-      }
-      lds_put<N, 2>(C, t1, t2, z);
-    }
-    sRed[tid] = p;
-    elem_sync<N>();
-    if (act && t == 0) {
-      double s = 0.0;
-      for (int j = 0; j < NN; ++j) s += sRed[el * NN + j];
-      parts[7 * e + slot] = s;
-    }
-  };
-  take(0);
-  face_term<N, 0, double, double, true>(m1, T, v, e, ex, ey, ez, X, sXn[le], 1.0, t1, t2, C, sF[le], act, 0);
-  take(1);
-  face_term<N, 0, double, double, true>(m1, T, v, e, ex, ey, ez, X, sXn[le], 1.0, t1, t2, C, sF[le], act, 1);
-  take(2);
-  face_term<N, 1, double, double, true>(m1, T, v, e, ex, ey, ez, X, sXn[le], 1.0, t1, t2, C, sF[le], act, 0);
-  take(3);
-  face_term<N, 1, double, double, true>(m1, T, v, e, ex, ey, ez, X, sXn[le], 1.0, t1, t2, C, sF[le], act, 1);
-  take(4);
-  face_term<N, 2, double, double, true>(m1, T, v, e, ex, ey, ez, X, sXn[le], 1.0, t1, t2, C, sF[le], act, 0);
-  take(5);
-  face_term<N, 2, double, double, true>(m1, T, v, e, ex, ey, ez, X, sXn[le], 1.0, t1, t2, C, sF[le], act, 1);
-  take(6);
+    for (int i = 0; i < N; ++i) p += uz[i] * c[i];
+    sRed[t] = p;
+  }
+  elem_sync<N>();
+  if (act && t == 0) {
+    double s = 0.0;
+    for (int j = 0; j < NN; ++j) s += sRed[j];
+    parts[7 * e] = s;
+  }
 }
 
 // g_T = K_T parts[T][0] + sum over faces (d, s) of dgamma/dtheta_T times the
-// whole unit-coefficient face form: the rows of T (parts of T) plus the rows
-// of the neighbour N (parts of N for its face (d, 1 - s)).
+// whole unit-coefficient face form (of a lower interior face: the neighbour's
+// part of its upper face).
 // dgamma/dtheta_T = gamma K_N / (K_T + K_N) on interior faces, K_T on boundary faces.
 __global__ __launch_bounds__(256) void k_dA_combine_trilinear(MeshArgs<double> m, const double* __restrict__ parts,
                                                               double* __restrict__ g) {
@@ -643,13 +356,12 @@ __global__ __launch_bounds__(256) void k_dA_combine_trilinear(MeshArgs<double> m
       if (d == 0) nb = neighbour<0>(m, ex, ey, ez, s);
       else if (d == 1) nb = neighbour<1>(m, ex, ey, ez, s);
       else nb = neighbour<2>(m, ex, ey, ez, s);
-      const double own = parts[7 * e + 1 + 2 * d + s];
       if (nb < 0) {
-        acc += K * own;
+        acc += K * parts[7 * e + 1 + 2 * d + s];
       } else {
         const double Kn = m.K[nb];
         const double gam = 2.0 * K * Kn / (K + Kn);
-        acc += gam * Kn / (K + Kn) * (own + parts[7 * nb + 1 + 2 * d + (1 - s)]);
+        acc += gam * Kn / (K + Kn) * parts[7 * (s ? e : nb) + 2 + 2 * d];
       }
     }
   g[e] = acc;
@@ -668,95 +380,65 @@ __global__ __launch_bounds__(256) void k_dA_combine_trilinear(MeshArgs<double> m
 //           and the flux terms twice, outward.
 // n^2 threads per element as in the apply: the six factors of a z-line are
 // formed from the line's Jacobian and contracted along z in registers, then
-// along y and x through LDS, grouped by their x table.  Summing all n^3
-// points for every DOF instead (6 n^3 multiply-adds per DOF) took 144 ms
-// against 1.20 ms on 48^3 Q7, and 1102 against 43 us on 23 x 18 x 21 Q4, now
-// with both inverses written in the same pass.
+// along y and x through LDS, grouped by their x table.  The face factors are
+// formed by points and contracted by whole lines with uniform tables.  Summing
+// all n^3 points for every DOF instead (6 n^3 multiply-adds per DOF) took 144 ms
+// against 1.13 ms on 48^3 Q7, and 1102 against 31 us on 23 x 18 x 21 Q4 (43 us
+// with the face contractions by points, a lane reading its own table row), both
+// inverses written in the same pass.  Vector instructions bound it.
+// The three point factors of the face normal to D on side s at the thread's
+// point (t1, t2) = (A, B): F0 (BB BB), F1 (BD along A), F2 (BD along B), n^2 each.
 template <int N, int D>
-__device__ void diag_face(const MeshArgs<double>& m, const Tables<double>& T, int64_t e, int ex, int ey, int ez,
-                          const double (&X)[8][3], double K, int t1, int t2, double* Y, double (*F)[N * N], bool act,
-                          int s) {
-  constexpr int NN = N * N, A = D == 0 ? 1 : 0, B = D == 2 ? 1 : 2, c1 = (D + 1) % 3, c2 = (D + 2) % 3;
+__device__ __forceinline__ void diag_face(const MeshArgs<double>& m, const Tables<double>& T, int64_t e, int ex, int ey,
+                                          int ez, const double (&X)[8][3], double K, int t1, int t2, double* F,
+                                          int s) {
+  constexpr int A = D == 0 ? 1 : 0, B = D == 2 ? 1 : 2, c1 = (D + 1) % 3, c2 = (D + 2) % 3;
   const int t = t1 + N * t2;
   const int end = s ? N - 1 : 0;
-  elem_sync<N>();  // face rows free, Y complete
-  if (act) {
-    const int64_t nb = neighbour<D>(m, ex, ey, ez, s);
-    const bool self = nb == e;  // one element along D, periodic
-    const double w = T.gw[t1] * T.gw[t2], sig = m.sig_hat / (D == 0 ? m.hx : (D == 1 ? m.hy : m.hz));
-    double J[3][3], Aj[3][3], Jo[3][3], Ao[3][3];
-    face_jacobian<D>(X, s, T.gx[t1], T.gx[t2], J);
-    adj3(J, Aj);
-    const double idet = 1.0 / det3(J);
-    double cDo = 0.0;
-    const bool other = self && s == 0;  // N dS is the upper side's
-    if (self) {
-      face_jacobian<D>(X, 1 - s, T.gx[t1], T.gx[t2], Jo);
-      adj3(Jo, Ao);
-    }
-    double Nv[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      const int p = (r + 1) % 3, q = (r + 2) % 3;
-      Nv[r] = other ? Jo[p][c1] * Jo[q][c2] - Jo[q][c1] * Jo[p][c2] : J[p][c1] * J[q][c2] - J[q][c1] * J[p][c2];
-    }
-    const double area = sqrt(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
-    double c[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) c[r] = (Aj[r][0] * Nv[0] + Aj[r][1] * Nv[1] + Aj[r][2] * Nv[2]) * idet;
-    // the other side of the element's own face: its normal derivative at the
-    // end node (its trace there is zero)
-    if (self) cDo = (Ao[D][0] * Nv[0] + Ao[D][1] * Nv[1] + Ao[D][2] * Nv[2]) / det3(Jo) * (s ? T.d0 : T.d1)[end];
-    double gam = K;
-    double fl = s ? -2.0 * K : 2.0 * K;  // Dirichlet: both flux terms, outward normal
-    if (nb >= 0) {
-      const double Kn = m.K[nb];
-      gam = 2.0 * K * Kn / (K + Kn);
-      fl = s ? -gam : gam;  // [phi] = phi on the upper face, -phi on the lower
-    }
-    F[0][t] = w * (sig * gam * area + fl * ((s ? T.d1 : T.d0)[end] * c[D] + cDo));
-    F[1][t] = w * fl * c[A];
-    F[2][t] = w * fl * c[B];
+  const int64_t nb = neighbour<D>(m, ex, ey, ez, s);
+  const bool self = nb == e;  // one element along D, periodic
+  const double w = T.gw[t1] * T.gw[t2], sig = m.sig_hat / (D == 0 ? m.hx : (D == 1 ? m.hy : m.hz));
+  double J[3][3], Aj[3][3], Jo[3][3], Ao[3][3];
+  face_jacobian<D>(X, s, T.gx[t1], T.gx[t2], J);
+  adj3(J, Aj);
+  const double idet = recip(det3(J));
+  double cDo = 0.0;
+  const bool other = self && s == 0;  // N dS is the upper side's
+  if (self) {
+    face_jacobian<D>(X, 1 - s, T.gx[t1], T.gx[t2], Jo);
+    adj3(Jo, Ao);
   }
-  elem_sync<N>();
-  if (act) {  // along t1: BB F0 + BD F1 and BB F2
-    double r0 = 0.0, r1 = 0.0;
+  double Nv[3];
 #pragma unroll
-    for (int q = 0; q < N; ++q) {
-      const double bb = T.BB[q * kMaxN + t1], bd = T.BD[q * kMaxN + t1];
-      r0 += bb * F[0][t2 * N + q] + bd * F[1][t2 * N + q];
-      r1 += bb * F[2][t2 * N + q];
-    }
-    F[3][t] = r0;
-    F[4][t] = r1;
+  for (int r = 0; r < 3; ++r) {
+    const int p = (r + 1) % 3, q = (r + 2) % 3;
+    Nv[r] = other ? Jo[p][c1] * Jo[q][c2] - Jo[q][c1] * Jo[p][c2] : J[p][c1] * J[q][c2] - J[q][c1] * J[p][c2];
   }
-  elem_sync<N>();
-  if (act) {  // along t2, into the end layer
-    double r = 0.0;
+  const double area = root(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
+  double c[3];
 #pragma unroll
-    for (int q = 0; q < N; ++q) r += T.BB[q * kMaxN + t2] * F[3][q * N + t1] + T.BD[q * kMaxN + t2] * F[4][q * N + t1];
-    Y[lds_idx<N, D, double>(t1, t2, end)] += r;
+  for (int r = 0; r < 3; ++r) c[r] = (Aj[r][0] * Nv[0] + Aj[r][1] * Nv[1] + Aj[r][2] * Nv[2]) * idet;
+  // the other side of the element's own face: its normal derivative at the
+  // end node (its trace there is zero)
+  if (self) cDo = (Ao[D][0] * Nv[0] + Ao[D][1] * Nv[1] + Ao[D][2] * Nv[2]) / det3(Jo) * (s ? T.d0 : T.d1)[end];
+  double gam = K;
+  double fl = s ? -2.0 * K : 2.0 * K;  // Dirichlet: both flux terms, outward normal
+  if (nb >= 0) {
+    const double Kn = m.K[nb];
+    gam = 2.0 * K * Kn / (K + Kn);
+    fl = s ? -gam : gam;  // [phi] = phi on the upper face, -phi on the lower
   }
-  (void)NN;
-}
-
-// out_i (+)= sum_q T_qi a_q along the line (T: one of the product tables)
-template <int N, bool ADD>
-__device__ __forceinline__ void prod_line(const double* T, const double (&a)[N], double (&out)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) {
-    double s = ADD ? out[i] : 0.0;
-#pragma unroll
-    for (int q = 0; q < N; ++q) s += T[q * kMaxN + i] * a[q];
-    out[i] = s;
-  }
+  F[t] = w * (sig * gam * area + fl * ((s ? T.d1 : T.d0)[end] * c[D] + cDo));
+  F[N * N + t] = w * fl * c[A];
+  F[2 * N * N + t] = w * fl * c[B];
 }
 
 template <int N>
 __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, DiagOut out, const int* run) {
   constexpr int NN = N * N, N3 = NN * N, EPB = elems_per_block(N), PE = Lay<N, double>::PE;
-  static_assert(5 * NN <= 2 * PE, "the face rows share two tiles");
-  __shared__ double sT[EPB * 3 * PE];
+  // three tiles; the point factors of the six faces (18 n^2) follow the first
+  constexpr int TE = 3 * PE > PE + 18 * NN ? 3 * PE : PE + 18 * NN;
+  __shared__ double sT[EPB * TE];
   __shared__ double sX[EPB][8][3];
   if (run != nullptr && *run == 0) return;
   const Tables<double>& T = *m.tab;
@@ -764,10 +446,9 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
   const int64_t e = (int64_t)blockIdx.x * EPB + el;
   const bool act = (el < EPB) && (e < m.E);
   const int le = act ? el : 0;
-  double* A = sT + le * 3 * PE;
+  double* A = sT + le * TE;
   double* B = A + PE;
   double* C = B + PE;
-  double(*F)[NN] = (double(*)[NN])B;
   int ex = 0, ey = 0, ez = 0;
   double K = 1.0;
   if (act) {
@@ -864,15 +545,75 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
     prod_line<N, true>(T.BB, v, acc);
     lds_put<N, 0>(A, t1, t2, acc);  // the thread's own x-line
   }
+  elem_sync<N>();
+  // faces: the point factors, then 6 n lines along A and 6 n along B with
+  // uniform tables; entry (t1, t2) of row r of face f = 2 D + s at (3 f + r) n^2 + t
+  double* F = A + PE;
+  if (act) {
 #pragma unroll
-  for (int s = 0; s < 2; ++s) {
-    diag_face<N, 0>(m, T, e, ex, ey, ez, X, K, t1, t2, A, F, act, s);
-    diag_face<N, 1>(m, T, e, ex, ey, ez, X, K, t1, t2, A, F, act, s);
-    diag_face<N, 2>(m, T, e, ex, ey, ez, X, K, t1, t2, A, F, act, s);
+    for (int s = 0; s < 2; ++s) {
+      diag_face<N, 0>(m, T, e, ex, ey, ez, X, K, t1, t2, F + 3 * s * NN, s);
+      __builtin_amdgcn_sched_barrier(0);  // face by face: fewer registers
+      diag_face<N, 1>(m, T, e, ex, ey, ez, X, K, t1, t2, F + (6 + 3 * s) * NN, s);
+      __builtin_amdgcn_sched_barrier(0);
+      diag_face<N, 2>(m, T, e, ex, ey, ez, X, K, t1, t2, F + (12 + 3 * s) * NN, s);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  elem_sync<N>();
+  if (act) {
+#pragma unroll 1
+    for (int q = t; q < 6 * N; q += NN) {  // along A: BB F0 + BD F1 to row 0, BB F2 to row 1
+      double* R = F + q / N * (3 * NN) + q % N * N;
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = R[i];
+      prod_line<N, false>(T.BB, v, w);
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = R[NN + i];
+      prod_line<N, true>(T.BD, v, w);
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        R[i] = w[i];
+        v[i] = R[2 * NN + i];
+      }
+      prod_line<N, false>(T.BB, v, w);
+#pragma unroll
+      for (int i = 0; i < N; ++i) R[NN + i] = w[i];
+    }
+  }
+  elem_sync<N>();
+  if (act) {
+#pragma unroll 1
+    for (int q = t; q < 6 * N; q += NN) {  // along B: BB row 0 + BD row 1 to row 2
+      double* R = F + q / N * (3 * NN) + q % N;
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = R[i * N];
+      prod_line<N, false>(T.BB, v, w);
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] = R[NN + i * N];
+      prod_line<N, true>(T.BD, v, w);
+#pragma unroll
+      for (int i = 0; i < N; ++i) R[2 * NN + i * N] = w[i];
+    }
+  }
+  elem_sync<N>();
+  if (act) {  // along x: the thread's own x-line (t1, t2) = (y, z)
+    A[lds_idx<N, 0, double>(t1, t2, 0)] += F[2 * NN + t];
+    A[lds_idx<N, 0, double>(t1, t2, N - 1)] += F[5 * NN + t];
   }
   elem_sync<N>();
   if (act) {
     lds_get<N, 2>(A, t1, t2, v);
+    if (t2 == 0) {  // along y: the layers y = 0 and y = n - 1
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] += F[8 * NN + t1 + N * i];
+    }
+    if (t2 == N - 1) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) v[i] += F[11 * NN + t1 + N * i];
+    }
+    v[0] += F[14 * NN + t];  // along z
+    v[N - 1] += F[17 * NN + t];
 #pragma unroll
     for (int i = 0; i < N; ++i) out.put(e * N3 + lidx<N, 2>(t1, t2, i), v[i]);
   }
@@ -945,8 +686,10 @@ template <int N>
 static hipError_t run_dA_tri(const MeshArgs<double>& m, const double* u, const double* v, double* parts, double* g,
                              hipStream_t s) {
   const int64_t nb = element_blocks(N, m.E);
+  hipError_t e = launch_tri_faces_dA(N, m, u, v, parts, s);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_dA_parts_trilinear<N>), dim3((unsigned)nb), dim3(kBlock), 0, s, m, u, v, parts);
-  hipError_t e = hipGetLastError();
+  e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dA_combine_trilinear, dim3((unsigned)((m.E + 255) / 256)), dim3(256), 0, s, m, parts, g);
   return hipGetLastError();

@@ -60,3 +60,17 @@ def test_solvers_next_to_the_face_rows(k):
         assert info["status"] == DG_OK, (prec, mode, var)
         assert np.linalg.norm(bs - A @ host(u)) <= 1.2e-10 * np.linalg.norm(bs), (prec, mode, var)
         assert torch.equal(op.apply(b), y)
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("shape,bc", [((7, 3, 2), "dirichlet"), ((5, 1, 4), "periodic")])
+def test_sensitivity_and_diagonal(shape, bc, k):
+    """dA/dtheta (1e-12) from one value per face and the diagonal (1e-13), every degree."""
+    banner(f"trilinear dA/dtheta, diagonal {shape} {bc} k={k}")
+    E = int(np.prod(shape))
+    theta, V = I.theta(E, seed=k), box_vertices(*shape, seed=k)
+    m = O.Mesh(*shape, k, bc=BCS[bc], theta=theta, vertices=V)
+    op = DGOperator(*shape, k, bc, theta=dev(theta), vertices=dev(V))
+    u, v = I.uniform_vector(m.ndof, seed=k), I.uniform_vector(m.ndof, seed=k + 20)
+    assert rel_l2(host(op.dA_dtheta(dev(u), dev(v))), O.dA_dtheta(m, u, v)) <= 1e-12
+    assert rel_l2(host(op.diagonal()), O.assemble(m).diagonal()) <= 1e-13
