@@ -106,23 +106,25 @@ def lib() -> ctypes.CDLL:
     return L
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream, *keep) -> ctypes.c_void_p:
-    """The HIP stream handle for a call.  When the work goes to a stream other
+def _stream(stream, *keep) -> int:
+    """The HIP stream handle for a call: the current stream's without making a
+    Stream object of it (an apply on the smallest meshes takes the GPU 5 us, as
+    long as the call itself), unless one is given.  When the work goes to a stream other
     than the current one, the tensors it uses (``keep``: outputs allocated
     here, contiguous temporaries, the workspace) are recorded on that stream,
     so the caching allocator does not hand their memory out again before the
     library's kernels on it have finished."""
-    cur = torch.cuda.current_stream()
-    s = stream if stream is not None else cur
-    if s != cur:
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if stream != torch.cuda.current_stream():
         for t in keep:
             if t is not None:
-                t.record_stream(s)
-    return ctypes.c_void_p(s.cuda_stream)
+                t.record_stream(stream)
+    return stream.cuda_stream
 
 
 def query_workspace(nx, ny, nz, degree, bc="dirichlet", trilinear=False, penalty_hat=0.0) -> int:
@@ -214,10 +216,13 @@ class DGOperator:
         bf16 (bfloat16 in, float out), bf16_mfma (as bf16, tangential masses on the
         matrix cores; affine meshes, degree <= 4)."""
         self._vec(x, _IN_DTYPE[prec])
-        y = torch.empty(self.ndof, dtype=_OUT_DTYPE[prec], device=x.device) if out is None else out
-        self._vec(y, _OUT_DTYPE[prec])
-        fn = lib().dg_apply_transpose if transpose else lib().dg_apply
-        self._check(fn(self._h, PREC[prec], _ptr(x), _ptr(y), _stream(stream, x, y, self.workspace)))
+        y = torch.empty(self.ndof, dtype=_OUT_DTYPE[prec], device=x.device) if out is None else \
+            self._vec(out, _OUT_DTYPE[prec])
+        L = lib()
+        fn = L.dg_apply_transpose if transpose else L.dg_apply
+        rc = fn(self._h, PREC[prec], x.data_ptr(), y.data_ptr(), _stream(stream, x, y, self.workspace))
+        if rc < 0:
+            self._check(rc)
         return y
 
     def apply_multi(self, X: torch.Tensor, prec: str = "f64", out: Optional[torch.Tensor] = None,
