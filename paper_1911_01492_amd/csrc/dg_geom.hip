@@ -17,34 +17,51 @@ __device__ __forceinline__ double corner_coord(const MeshArgs<double>& m, int cx
 }
 
 // x = sum_c X_c prod_d (c_d ? xi_d : 1 - xi_d) at the Gauss points, one thread
-// per coordinate, so that the stores of a wave are one contiguous run (the
-// kernel is bound by its 24 bytes per point).  A block takes the elements
-// that give it about 256 points; the corners are staged in LDS once.
-// (24^3 Q5: 31 -> 25 us, against one thread per point and 24-byte strides)
-__host__ __device__ constexpr int qp_elems(int n) { return n * n * n >= kBlock ? 1 : kBlock / (n * n * n); }
+// per x-row of n points: along it a coordinate is p + xi_0 d, p and d bilinear
+// in (xi_1, xi_2).  The rows are collected in LDS and leave as one contiguous
+// run, two values per lane (the kernel is bound by its 24 bytes per point).
+// (24^3 Q5, 72 MB: one thread per point and 24-byte strides 31 us, one thread per
+// coordinate 24, this 15)
 template <int N>
 __global__ __launch_bounds__(kBlock) void k_quad_points(MeshArgs<double> m, double* __restrict__ xq) {
-  constexpr int N3 = N * N * N, G = qp_elems(N);
-  __shared__ double sX[G * 24], sg[N];
-  const int64_t e0 = (int64_t)blockIdx.x * G;
-  const int ne = (int)(m.E - e0 < G ? m.E - e0 : G), tid = threadIdx.x;
-  if (tid < N) sg[tid] = m.tab->gx[tid];
+  constexpr int NN = N * N, R = 3 * N, RS = R | 1, EPB = elems_per_block(N);
+  typedef double pair_t __attribute__((ext_vector_type(2), aligned(8)));
+  __shared__ double sX[EPB * 24], sO[EPB * NN * RS];
+  const int64_t e0 = (int64_t)blockIdx.x * EPB;
+  const int ne = (int)(m.E - e0 < EPB ? m.E - e0 : EPB), tid = threadIdx.x;
   for (int i = tid; i < ne * 24; i += kBlock) {
     const int64_t e = e0 + i / 24;
     const int ex = (int)(e % m.nx), ey = (int)((e / m.nx) % m.ny), ez = (int)(e / ((int64_t)m.nx * m.ny));
-    // coordinate-major: the 8 corners of one coordinate are adjacent
-    sX[i] = corner_coord(m, ex, ey, ez, i % 8, (i % 24) / 8);
+    sX[i] = corner_coord(m, ex, ey, ez, (i % 24) / 3, i % 3);  // 3 corner + coordinate
   }
   __syncthreads();
-  double* out = xq + e0 * (3 * N3);
-  for (int j = tid; j < ne * 3 * N3; j += kBlock) {
-    const int el = j / (3 * N3), r = j - el * (3 * N3), q = r / 3, a = r - 3 * q;
-    const double* X = sX + el * 24 + a * 8;
-    const double x0 = sg[q % N], x1 = sg[(q / N) % N], x2 = sg[q / (N * N)];
-    const double y0 = 1.0 - x0, y1 = 1.0 - x1, y2 = 1.0 - x2;
-    const double lo = y1 * (y0 * X[0] + x0 * X[1]) + x1 * (y0 * X[2] + x0 * X[3]);
-    const double hi = y1 * (y0 * X[4] + x0 * X[5]) + x1 * (y0 * X[6] + x0 * X[7]);
-    out[j] = y2 * lo + x2 * hi;
+  const Tables<double>& T = *m.tab;
+  if (tid < ne * NN) {
+    const int el = tid / NN, t = tid - el * NN;
+    const double x1 = T.gx[t % N], x2 = T.gx[t / N], y1 = 1.0 - x1, y2 = 1.0 - x2;
+    double* o = sO + tid * RS;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      const double* X = sX + el * 24 + a;
+      const double p = y2 * (y1 * X[0] + x1 * X[6]) + x2 * (y1 * X[12] + x1 * X[18]);
+      const double r = y2 * (y1 * X[3] + x1 * X[9]) + x2 * (y1 * X[15] + x1 * X[21]);
+#pragma unroll
+      for (int i = 0; i < N; ++i) o[3 * i + a] = (1.0 - T.gx[i]) * p + T.gx[i] * r;
+    }
+  }
+  __syncthreads();
+  double* out = xq + e0 * (NN * R);
+  const int tot = ne * NN * R;
+  for (int j = 2 * tid; j < tot; j += 2 * kBlock) {
+    const int r0 = j / R, r1 = (j + 1) / R;
+    if (j + 1 < tot) {
+      pair_t v;
+      v.x = sO[j + r0 * (RS - R)];
+      v.y = sO[j + 1 + r1 * (RS - R)];
+      *(pair_t*)(out + j) = v;
+    } else {
+      out[j] = sO[j + r0 * (RS - R)];
+    }
   }
 }
 
@@ -108,8 +125,7 @@ __global__ __launch_bounds__(kBlock) void k_load_vector(MeshArgs<double> m, cons
 
 template <int N>
 static hipError_t run_qp(const MeshArgs<double>& m, double* xq, hipStream_t s) {
-  const int64_t nb = (m.E + qp_elems(N) - 1) / qp_elems(N);
-  hipLaunchKernelGGL((k_quad_points<N>), dim3((unsigned)nb), dim3(kBlock), 0, s, m, xq);
+  hipLaunchKernelGGL((k_quad_points<N>), dim3((unsigned)element_blocks(N, m.E)), dim3(kBlock), 0, s, m, xq);
   return hipGetLastError();
 }
 template <int N>
