@@ -56,13 +56,14 @@
 #include "dg_kernels.hpp"
 #include "dg_lines.hpp"
 #include "dg_faces.hpp"
+#include "dg_tables.hpp"
 
 namespace dg {
 
 // out = C a along the line (C centro-antisymmetric: even-odd halves from n = 4,
 // where they cost no more operations and hold half the table in scalar registers)
-template <int N, typename TC>
-__device__ __forceinline__ void cd_line(const Tables<TC>& T, const TC (&a)[N], TC (&out)[N]) {
+template <int N, typename TC, typename TT>
+__device__ __forceinline__ void cd_line(const TT& T, const TC (&a)[N], TC (&out)[N]) {
   if constexpr (N >= 4) {
     contract_eo<N, TC, -1>(T.eC, a, out);
   } else {
@@ -125,11 +126,20 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   // their address, which keeps the compiler from holding every table in
   // scalar registers across the whole kernel (at n >= 4 they do not fit and
   // spill into vector-register lanes): a phase loads the tables it uses.
-  auto tabs = [&]() -> const Tables<TC>& {
-    uint64_t a = (uint64_t)m.tab;
-    asm volatile("" : "+s"(a));
-    typedef const __attribute__((address_space(4))) Tables<TC>* ConstTab;
-    return *(const Tables<TC>*)(ConstTab)a;
+  // FP32 from n = 6: compile-time constants, literals of the instructions (23^3 Q6
+  // 34.3 -> 31.2 us, 42^3 Q6 176 -> 163, 49^3 Q5 141 -> 134, 20^3 Q7 23.2 -> 21.9; up to
+  // n = 5 from -4 to +3%, and in FP64 a literal takes two scalar moves).
+  constexpr bool CTAB = sizeof(TC) == 4 && N >= 6;
+  [[maybe_unused]] constexpr KTables<TC> ktab = CTAB ? ctab::make<N, TC>() : KTables<TC>{};
+  auto tabs = [&]() -> decltype(auto) {
+    if constexpr (CTAB) {
+      return (ktab);
+    } else {
+      uint64_t a = (uint64_t)m.tab;
+      asm volatile("" : "+s"(a));
+      typedef const __attribute__((address_space(4))) Tables<TC>* ConstTab;
+      return *(const Tables<TC>*)(ConstTab)a;
+    }
   };
   const int tb = (int)xcd_remap(blockIdx.x, gridDim.x);
   int o[3];
@@ -150,7 +160,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   TC* Fe = F + el * FS;
   TC* P = sP + el * PR * NN;
   TC* ZR = ZR_IN_F ? Fe : P + 4 * NN;  // the element's z-face rows: lower side, then upper side
-  if (tid < NN) sC[tid] = tabs().Cd[(tid / N) * kMaxN + tid % N];
+  if (tid < NN) sC[tid] = m.tab->Cd[(tid / N) * kMaxN + tid % N];
   const int64_t e = c[0] + (int64_t)m.nx * (c[1] + (int64_t)m.ny * c[2]);
   const uint32_t eo = (uint32_t)e * (uint32_t)N3;  // the element's first entry (N_dof < 2^31)
   const TC K = m.K[e], K2 = TC(-2) * K;
@@ -160,7 +170,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   TC jxl, jxh;  // this thread's x-face jumps at (y, z) = (t1, t2), used again in X2 and X3
   // ---------------- X: b_x -> S1, x-face rows and jumps
   {
-    const Tables<TC>& T = tabs();
+    const auto& T = tabs();
     const TC GL = gco(0), GH = gco(1);
     face_phase<N, 0, BX, BY, BZ, FS, TC, TIN, false, OFF32>(m, T, x, own, eo, c, o, Nd, t, t1, t2, Fe, K, GL, GH,
                                                             TC(0), b, u, tr);
@@ -173,7 +183,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   lds_sync<XROW>();  // F (read by the x-neighbours) is rewritten by the next phase
   // ---------------- Y: b_y -> S2, S1 <- M_y S1, c_y -> S3, y-face jumps
   {
-    const Tables<TC>& T = tabs();
+    const auto& T = tabs();
     const TC GL = gco(2), GH = gco(3);
     face_phase<N, 1, BX, BY, BZ, FS, TC, TIN, false, OFF32>(m, T, x, own, eo, c, o, Nd, t, t1, t2, Fe, K, GL, GH,
                                                             TC(0), b, u, tr);
@@ -194,7 +204,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   lds_sync<ELEM>();
   // ---------------- X2: S1 <- S1 + M_x S2 + G_xy P_xy,  P_xy = C_x c_y + C_y (x-face rows) + corners
   {
-    const Tables<TC>& T = tabs();
+    const auto& T = tabs();
     lds_get<N, 0, TC, LV>(S2, t1, t2, v);
     lds_get<N, 0, TC, LV>(S1, t1, t2, w);
     mass_line<N, TC, false>(T, v, b);
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   // ---------------- Z: b_z -> S2, r = M_z S1, P_yz -> S1, c_z -> S3, z-face rows and jumps
   TC r[N];
   {
-    const Tables<TC>& T = tabs();
+    const auto& T = tabs();
     const TC GL = gco(4), GH = gco(5);
     const TC cr = m.R ? m.R[e] * m.vol : TC(0);
     face_phase<N, 2, BX, BY, BZ, FS, TC, TIN, false, OFF32>(m, T, x, own, eo, c, o, Nd, t, t1, t2, Fe, K, GL, GH,
@@ -284,7 +294,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   // ---------------- X3: S2 <- M_x S2 + G_xz P_xz (P_xz = C_x c_z + C_z (x-face rows) + corners),
   //                      S1 <- G_yz M_x S1
   {
-    const Tables<TC>& T = tabs();
+    const auto& T = tabs();
     lds_get<N, 0, TC, LV>(S2, t1, t2, v);
     mass_line<N, TC, false>(T, v, w);
     lds_get<N, 0, TC, LV>(S3, t1, t2, v);
@@ -318,7 +328,7 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   lds_sync<ELEM>();
   // ---------------- Y3: S2 <- M_y S2
   {
-    const Tables<TC>& T = tabs();
+    const auto& T = tabs();
     lds_get<N, 1, TC, LV>(S2, t1, t2, v);
     mass_line<N, TC, false>(T, v, w);
     lds_put<N, 1, TC, LV>(S2, t1, t2, w);
@@ -330,13 +340,11 @@ __global__ __launch_bounds__(apply_block(N)) void k_apply_ppd(MeshArgs<TC> m, co
   lds_get<N, 2, TC, LV>(S1, t1, t2, w);
   if (act) {
     const uint32_t yb = (eo + (uint32_t)lidx<N, 2>(t1, t2, 0)) * (uint32_t)sizeof(TOUT);
-    TOUT* py = y + e * N3;
+    TOUT* py = OFF32 ? (TOUT*)((char*)y + (size_t)yb) : y + e * N3 + lidx<N, 2>(t1, t2, 0);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const TOUT yv = (TOUT)(r[i] + v[i] + w[i]);
-      TOUT* dst = OFF32 ? (TOUT*)((char*)y + (yb + (uint32_t)(lidx<N, 2>(0, 0, i) * sizeof(TOUT))))
-                        : &py[lidx<N, 2>(t1, t2, i)];
-      __builtin_nontemporal_store(yv, dst);
+      __builtin_nontemporal_store(yv, py + lidx<N, 2>(0, 0, i));
       if (DOT) part += (double)u[i] * (double)yv;
     }
   }

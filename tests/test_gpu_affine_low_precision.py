@@ -43,3 +43,21 @@ def test_f32_and_bf16(shape, bc, k):
     Y = host(op.apply_multi(torch.stack([dev(x32, torch.float32), dev(-2 * x32, torch.float32)]), prec="f32"))
     r = A @ x32.astype(np.float64)
     assert rel_l2(Y.reshape(2, -1), np.stack([r, -2 * r])) <= 2e-5
+
+
+@pytest.mark.parametrize("k", [5, 6, 7])
+@pytest.mark.parametrize("shape,bc", [((3, 2, 2), "dirichlet"), ((1, 3, 2), "periodic")])
+def test_parallelepipeds_with_constant_tables(shape, bc, k):
+    """Equal parallelepipeds in FP32, whose tables are constants from n = 6 on; the same bar."""
+    banner(f"low precision parallelepipeds {shape} {bc} k={k}")
+    V = I.uniform_vertices(*shape) @ np.array([[1.0, 0.3, -0.2], [0.1, 0.9, 0.25], [-0.15, 0.2, 1.1]]).T
+    theta = I.theta(int(np.prod(shape)), seed=k)
+    A = O.assemble(m := O.Mesh(*shape, k, bc=BCS[bc], theta=theta, vertices=V))
+    op = DGOperator(*shape, k, bc, theta=dev(theta), vertices=dev(V))
+    assert op.kernel == "parallelepiped"
+    x = I.uniform_vector(m.ndof, seed=k)
+    x32, bits = I.to_f32(x), I.to_bf16_bits(x)
+    y = host(op.apply(dev(x32, torch.float32), prec="f32"))
+    assert rel_l2(y, A @ x32.astype(np.float64)) <= 2e-5
+    y = host(op.apply(bf16_dev(bits), prec="bf16"))
+    assert rel_l2(y, A @ I.bf16_bits_to_f64(bits)) <= 2e-5
