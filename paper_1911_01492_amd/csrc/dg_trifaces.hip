@@ -24,12 +24,12 @@
 //
 // With one thread per face point instead (each output a dot product of n LDS
 // values with a table row of the thread's own, in one kernel with the volume
-// part) an apply of 48^3 Q7 took 1500 us; with this kernel 978 us (faces 490,
+// part) an apply of 48^3 Q7 took 1500 us; with this kernel 960 us (faces 460,
 // volume 495), against 264 us for its 1.3 GB at the rate of a large copy.
 // FP64 arithmetic bounds it: at n = 8 1900 vector instructions per wave, 57 % of
 // the cycles at three waves per SIMD (about 100 of them per face point for the
 // two conormals, 1 / det, |N| and the exchange); the address unit is busy 45 %.
-// Others, apply before -> now: 73^3 Q3 823 -> 688 us, 58^3 Q4 862 -> 677, 42^3 Q6
+// Others, apply before -> now: 73^3 Q3 823 -> 688 us, 58^3 Q4 862 -> 663, 42^3 Q6
 // 797 -> 617, 146^3 Q1 2022 -> 1486; FP32 37^3 Q7 322 -> 244.
 #include "dg_internal.hpp"
 #include "dg_kernels.hpp"
@@ -411,7 +411,9 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
       gd[i] = co * cd;
       ga[i] = co * ca;
       gb[i] = co * cb;
-      if (N == 8 || N == 5) __builtin_amdgcn_sched_barrier(0);  // point by point: no spills at 168 (128) registers
+      // points in groups: no spills at 168 (n = 8) and 128 (n = 5) registers (one by
+      // one the faces of 48^3 Q7 took 497 us, by four 450)
+      if (sizeof(TC) == 8 && ((N == 8 && i == 3) || (N == 5 && (i & 1)))) __builtin_amdgcn_sched_barrier(0);
     }
   }
   {  // along axis B: x = P + Dg^T Rb; from D = 1 on B^T x, B^T Ra, B^T Rd
