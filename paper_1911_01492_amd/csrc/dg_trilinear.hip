@@ -383,54 +383,47 @@ __global__ __launch_bounds__(256) void k_dA_combine_trilinear(MeshArgs<double> m
 // along y and x through LDS, grouped by their x table.  The face factors are
 // formed by points and contracted by whole lines with uniform tables.  Summing
 // all n^3 points for every DOF instead (6 n^3 multiply-adds per DOF) took 144 ms
-// against 1.13 ms on 48^3 Q7, and 1102 against 31 us on 23 x 18 x 21 Q4 (43 us
+// against 0.93 ms on 48^3 Q7, and 1102 against 28 us on 23 x 18 x 21 Q4 (43 us
 // with the face contractions by points, a lane reading its own table row), both
 // inverses written in the same pass.  Vector instructions bound it.
 // The three point factors of the face normal to D on side s at the thread's
 // point (t1, t2) = (A, B): F0 (BB BB), F1 (BD along A), F2 (BD along B), n^2 each.
 template <int N, int D>
 __device__ __forceinline__ void diag_face(const MeshArgs<double>& m, const Tables<double>& T, int64_t e, int ex, int ey,
-                                          int ez, const double (&X)[8][3], double K, int t1, int t2, double* F,
-                                          int s) {
-  constexpr int A = D == 0 ? 1 : 0, B = D == 2 ? 1 : 2, c1 = (D + 1) % 3, c2 = (D + 2) % 3;
+                                          int ez, const double (&X)[8][3], int t1, int t2, double* F, int s) {
+  constexpr int A = D == 0 ? 1 : 0, B = D == 2 ? 1 : 2;
   const int t = t1 + N * t2;
   const int end = s ? N - 1 : 0;
-  const int64_t nb = neighbour<D>(m, ex, ey, ez, s);
-  const bool self = nb == e;  // one element along D, periodic
-  const double w = T.gw[t1] * T.gw[t2], sig = m.sig_hat / (D == 0 ? m.hx : (D == 1 ? m.hy : m.hz));
-  double J[3][3], Aj[3][3], Jo[3][3], Ao[3][3];
+  const int nD = D == 0 ? m.nx : (D == 1 ? m.ny : m.nz), c = D == 0 ? ex : (D == 1 ? ey : ez);
+  const bool has = m.periodic || (s ? c < nD - 1 : c > 0);
+  const bool self = m.periodic && nD == 1;  // one element along D, periodic
+  const double w = T.gw[t1] * T.gw[t2], G = m.G[6 * e + 2 * D + s];
+  double J[3][3], Aj[3][3];
   face_jacobian<D>(X, s, T.gx[t1], T.gx[t2], J);
   adj3(J, Aj);
-  const double idet = recip(det3(J));
-  double cDo = 0.0;
-  const bool other = self && s == 0;  // N dS is the upper side's
+  const double idet = recip(J[0][D] * Aj[D][0] + J[1][D] * Aj[D][1] + J[2][D] * Aj[D][2]);
+  // N dS is row D of adj J (of the upper side's on the element's own face)
+  double Nv[3] = {Aj[D][0], Aj[D][1], Aj[D][2]}, cDo = 0.0;
   if (self) {
+    double Jo[3][3], Ao[3][3];
     face_jacobian<D>(X, 1 - s, T.gx[t1], T.gx[t2], Jo);
     adj3(Jo, Ao);
-  }
-  double Nv[3];
+    if (s == 0) {
 #pragma unroll
-  for (int r = 0; r < 3; ++r) {
-    const int p = (r + 1) % 3, q = (r + 2) % 3;
-    Nv[r] = other ? Jo[p][c1] * Jo[q][c2] - Jo[q][c1] * Jo[p][c2] : J[p][c1] * J[q][c2] - J[q][c1] * J[p][c2];
+      for (int r = 0; r < 3; ++r) Nv[r] = Ao[D][r];
+    }
+    // the other side of the face: its normal derivative at the end node (its trace there is zero)
+    cDo = (Ao[D][0] * Nv[0] + Ao[D][1] * Nv[1] + Ao[D][2] * Nv[2]) / det3(Jo) * (s ? T.d0 : T.d1)[end];
   }
-  const double area = root(Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2]);
-  double c[3];
-#pragma unroll
-  for (int r = 0; r < 3; ++r) c[r] = (Aj[r][0] * Nv[0] + Aj[r][1] * Nv[1] + Aj[r][2] * Nv[2]) * idet;
-  // the other side of the element's own face: its normal derivative at the
-  // end node (its trace there is zero)
-  if (self) cDo = (Ao[D][0] * Nv[0] + Ao[D][1] * Nv[1] + Ao[D][2] * Nv[2]) / det3(Jo) * (s ? T.d0 : T.d1)[end];
-  double gam = K;
-  double fl = s ? -2.0 * K : 2.0 * K;  // Dirichlet: both flux terms, outward normal
-  if (nb >= 0) {
-    const double Kn = m.K[nb];
-    gam = 2.0 * K * Kn / (K + Kn);
-    fl = s ? -gam : gam;  // [phi] = phi on the upper face, -phi on the lower
-  }
-  F[t] = w * (sig * gam * area + fl * ((s ? T.d1 : T.d0)[end] * c[D] + cDo));
-  F[N * N + t] = w * fl * c[A];
-  F[2 * N * N + t] = w * fl * c[B];
+  const double NN2 = Nv[0] * Nv[0] + Nv[1] * Nv[1] + Nv[2] * Nv[2];
+  const double pen = (D == 0 ? m.sg[0] : (D == 1 ? m.sg[1] : m.sg[2])) * G * (has ? 2.0 : 1.0);
+  // [phi] = phi on the upper face, -phi on the lower; on a Dirichlet face both
+  // flux terms, outward normal: 2 G in either case
+  const double fl = s ? -2.0 * G : 2.0 * G, wf = w * fl * idet;
+  const double cD = self ? Aj[D][0] * Nv[0] + Aj[D][1] * Nv[1] + Aj[D][2] * Nv[2] : NN2;
+  F[t] = w * (pen * root(NN2) + fl * ((s ? T.d1 : T.d0)[end] * cD * idet + cDo));
+  F[N * N + t] = wf * (Aj[A][0] * Nv[0] + Aj[A][1] * Nv[1] + Aj[A][2] * Nv[2]);
+  F[2 * N * N + t] = wf * (Aj[B][0] * Nv[0] + Aj[B][1] * Nv[1] + Aj[B][2] * Nv[2]);
 }
 
 template <int N>
@@ -442,6 +435,14 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
   __shared__ double sX[EPB][8][3];
   if (run != nullptr && *run == 0) return;
   const Tables<double>& T = *m.tab;
+  // the product tables, through an address derived anew at each use (all of them
+  // do not fit in scalar registers at once)
+  auto tabs = [&]() -> const Tables<double>& {
+    uint64_t a = (uint64_t)m.tab;
+    asm volatile("" : "+s"(a));
+    typedef const __attribute__((address_space(4))) Tables<double>* ConstTab;
+    return *(const Tables<double>*)(ConstTab)a;
+  };
   const int tid = threadIdx.x, el = tid / NN, t = tid % NN, t1 = t % N, t2 = t / N;
   const int64_t e = (int64_t)blockIdx.x * EPB + el;
   const bool act = (el < EPB) && (e < m.E);
@@ -473,7 +474,8 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
       double J[3][3], Aj[3][3];
       jz.at(T.gx[q], J);
       adj3(J, Aj);
-      const double dJ = fabs(det3(J)), c = wq * T.gw[q] / dJ, cr = cw * T.gw[q] * dJ;
+      const double dJ = fabs(J[0][0] * Aj[0][0] + J[1][0] * Aj[0][1] + J[2][0] * Aj[0][2]);
+      const double c = wq * T.gw[q] * recip(dJ), cr = cw * T.gw[q] * dJ;
       auto G = [&](int r, int s2) { return c * (Aj[r][0] * Aj[s2][0] + Aj[r][1] * Aj[s2][1] + Aj[r][2] * Aj[s2][2]); };
       const double g00 = G(0, 0), g01 = 2.0 * G(0, 1), g02 = 2.0 * G(0, 2), g11 = G(1, 1), g12 = 2.0 * G(1, 2),
                    g22 = G(2, 2);
@@ -495,13 +497,13 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
   elem_sync<N>();
   if (act) {
     lds_get<N, 1>(A, t1, t2, v);
-    prod_line<N, false>(T.BB, v, w);
+    prod_line<N, false>(tabs().BB, v, w);
     lds_put<N, 1>(A, t1, t2, w);
   }
   elem_sync<N>();
   if (act) {
     lds_get<N, 0>(A, t1, t2, v);
-    prod_line<N, false>(T.DD, v, acc);
+    prod_line<N, false>(tabs().DD, v, acc);
   }
   elem_sync<N>();
   // x table BD: a01 (y: BD) + a02 (y: BB)
@@ -512,15 +514,15 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
   elem_sync<N>();
   if (act) {
     lds_get<N, 1>(A, t1, t2, v);
-    prod_line<N, false>(T.BD, v, w);
+    prod_line<N, false>(tabs().BD, v, w);
     lds_get<N, 1>(B, t1, t2, v);
-    prod_line<N, true>(T.BB, v, w);
+    prod_line<N, true>(tabs().BB, v, w);
     lds_put<N, 1>(A, t1, t2, w);
   }
   elem_sync<N>();
   if (act) {
     lds_get<N, 0>(A, t1, t2, v);
-    prod_line<N, true>(T.BD, v, acc);
+    prod_line<N, true>(tabs().BD, v, acc);
   }
   elem_sync<N>();
   // x table BB: a11 (y: DD) + a12 (y: BD) + a22 (y: BB)
@@ -532,17 +534,17 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
   elem_sync<N>();
   if (act) {
     lds_get<N, 1>(A, t1, t2, v);
-    prod_line<N, false>(T.DD, v, w);
+    prod_line<N, false>(tabs().DD, v, w);
     lds_get<N, 1>(B, t1, t2, v);
-    prod_line<N, true>(T.BD, v, w);
+    prod_line<N, true>(tabs().BD, v, w);
     lds_get<N, 1>(C, t1, t2, v);
-    prod_line<N, true>(T.BB, v, w);
+    prod_line<N, true>(tabs().BB, v, w);
     lds_put<N, 1>(A, t1, t2, w);
   }
   elem_sync<N>();
   if (act) {
     lds_get<N, 0>(A, t1, t2, v);
-    prod_line<N, true>(T.BB, v, acc);
+    prod_line<N, true>(tabs().BB, v, acc);
     lds_put<N, 0>(A, t1, t2, acc);  // the thread's own x-line
   }
   elem_sync<N>();
@@ -552,11 +554,11 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
   if (act) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      diag_face<N, 0>(m, T, e, ex, ey, ez, X, K, t1, t2, F + 3 * s * NN, s);
+      diag_face<N, 0>(m, T, e, ex, ey, ez, X, t1, t2, F + 3 * s * NN, s);
       __builtin_amdgcn_sched_barrier(0);  // face by face: fewer registers
-      diag_face<N, 1>(m, T, e, ex, ey, ez, X, K, t1, t2, F + (6 + 3 * s) * NN, s);
+      diag_face<N, 1>(m, T, e, ex, ey, ez, X, t1, t2, F + (6 + 3 * s) * NN, s);
       __builtin_amdgcn_sched_barrier(0);
-      diag_face<N, 2>(m, T, e, ex, ey, ez, X, K, t1, t2, F + (12 + 3 * s) * NN, s);
+      diag_face<N, 2>(m, T, e, ex, ey, ez, X, t1, t2, F + (12 + 3 * s) * NN, s);
       __builtin_amdgcn_sched_barrier(0);
     }
   }
@@ -567,16 +569,16 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
       double* R = F + q / N * (3 * NN) + q % N * N;
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = R[i];
-      prod_line<N, false>(T.BB, v, w);
+      prod_line<N, false>(tabs().BB, v, w);
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = R[NN + i];
-      prod_line<N, true>(T.BD, v, w);
+      prod_line<N, true>(tabs().BD, v, w);
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         R[i] = w[i];
         v[i] = R[2 * NN + i];
       }
-      prod_line<N, false>(T.BB, v, w);
+      prod_line<N, false>(tabs().BB, v, w);
 #pragma unroll
       for (int i = 0; i < N; ++i) R[NN + i] = w[i];
     }
@@ -588,10 +590,10 @@ __global__ __launch_bounds__(kBlock) void k_diag_trilinear(MeshArgs<double> m, D
       double* R = F + q / N * (3 * NN) + q % N;
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = R[i * N];
-      prod_line<N, false>(T.BB, v, w);
+      prod_line<N, false>(tabs().BB, v, w);
 #pragma unroll
       for (int i = 0; i < N; ++i) v[i] = R[NN + i * N];
-      prod_line<N, true>(T.BD, v, w);
+      prod_line<N, true>(tabs().BD, v, w);
 #pragma unroll
       for (int i = 0; i < N; ++i) R[2 * NN + i * N] = w[i];
     }
