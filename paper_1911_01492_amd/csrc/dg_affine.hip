@@ -35,6 +35,7 @@
 #include "dg_lines.hpp"
 #include "dg_faces.hpp"
 #include "dg_tables.hpp"
+#include "dg_planes.hpp"
 
 namespace dg {
 

@@ -826,7 +826,7 @@ int dg_apply_multi(dg_ctx* c, int prec, int transpose, int nrhs, const void* X, 
     HIP_TRY(c, launch_apply_ppd_multi(c->n, prec, nrhs, ppd_args(c, args64(c)), ppd_args(c, args32(c)), X, Y, s));
     return DG_OK;
   }
-  if (c->trilinear) {  // the two-pass apply shares its face buffer: one vector after the other
+  if (c->trilinear) {  // the applies share the face rows: one vector after the other
     for (int j = 0; j < nrhs; ++j)
       HIP_TRY(c, apply_any(c, prec, transpose, 0, xb + (size_t)j * c->ndof * ein, (char*)Y + (size_t)j * c->ndof * eout,
                            nullptr, 0, nullptr, s));

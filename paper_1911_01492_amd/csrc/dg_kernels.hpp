@@ -47,7 +47,7 @@ hipError_t launch_apply_affine(int n, int prec, int trans, int dot, const MeshAr
 bool mfma_apply_supported(int n);
 hipError_t launch_apply_affine_mfma(int n, int dot, const MeshArgs<float>& m, const uint16_t* x, float* y,
                                     double* partials, const int* skip, hipStream_t s, int nrhs = 1);
-// the same with element planes in registers (dg_planes.hip), for the meshes
+// the same with element planes in registers (dg_planes.hpp), for the meshes
 // that use_planes names: partials only (plane_blocks of them), nrhs vectors as
 // the second grid dimension
 __host__ __device__ constexpr int plane_by(int n) { return n == 2 ? 8 : 4; }  // elements of a wave's tile along y (4 along x)

@@ -1,4 +1,4 @@
-// dg_planes.hip -- sum-factorised SWIPDG apply y = A x on affine
+// dg_planes.hpp -- sum-factorised SWIPDG apply y = A x on affine
 // (axis-parallel box) elements for n = 2, 3, 4 nodes per direction, with whole
 // element planes in registers.
 //
@@ -30,6 +30,9 @@
 // 135 -> 83, BF16 116 -> 73; 73^3 Q3 FP32 89 -> 75, BF16 77 -> 57.  In FP64 at
 // n = 4 the planes take all 256 VGPRs and it ties with the line kernel (149 vs
 // 152), so it is not built there.
+// Part of the translation unit dg_affine.hip.
+#pragma once
+
 #include "dg_internal.hpp"
 #include "dg_kernels.hpp"
 #include "dg_lines.hpp"

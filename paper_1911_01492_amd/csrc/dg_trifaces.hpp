@@ -1,4 +1,4 @@
-// dg_trifaces.hip -- face terms of the trilinear apply: the first of its two
+// dg_trifaces.hpp -- face terms of the trilinear apply: the first of its two
 // kernels (the second, in dg_trilinear.hip, adds them to the volume part), and
 // of the sensitivity dA/dtheta.
 //
@@ -25,12 +25,16 @@
 // With one thread per face point instead (each output a dot product of n LDS
 // values with a table row of the thread's own, in one kernel with the volume
 // part) an apply of 48^3 Q7 took 1500 us; with this kernel 960 us (faces 460,
-// volume 495), against 264 us for its 1.3 GB at the rate of a large copy.
+// volume 495), against 450 us for its arithmetic (581 flop per DOF) at the rate of a
+// large FP64 product; the two kernels move 3.2 GB.
 // FP64 arithmetic bounds it: at n = 8 1900 vector instructions per wave, 57 % of
 // the cycles at three waves per SIMD (about 100 of them per face point for the
 // two conormals, 1 / det, |N| and the exchange); the address unit is busy 45 %.
 // Others, apply before -> now: 73^3 Q3 823 -> 688 us, 58^3 Q4 862 -> 663, 42^3 Q6
 // 797 -> 617, 146^3 Q1 2022 -> 1486; FP32 37^3 Q7 322 -> 244.
+// Part of the translation unit dg_trilinear.hip.
+#pragma once
+
 #include "dg_internal.hpp"
 #include "dg_kernels.hpp"
 #include "dg_lines.hpp"

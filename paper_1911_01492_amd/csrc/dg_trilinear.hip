@@ -8,7 +8,7 @@
 //   g    = G_q gr,  G_q = w_q K |det J| J^{-1} J^{-T} = w_q K adj(J) adj(J)^T / |det J|
 //   y    = (B^T (x) B^T (x) B^T) (sum_d Dg_d^T g_d + c w_q |det J| v)
 // (the last term is the optional reaction, c = 0 without it)
-// Faces: k_tri_faces (dg_trifaces.hip) runs first and leaves every element its
+// Faces: k_tri_faces (dg_trifaces.hpp) runs first and leaves every element its
 // six faces' rows in the workspace; they join the transposed contractions of
 // the volume part along the lines of their axis, so they cost no exchange of
 // their own.
@@ -19,6 +19,7 @@
 #include "dg_kernels.hpp"
 #include "dg_lines.hpp"
 #include "dg_geom.hpp"
+#include "dg_trifaces.hpp"
 
 namespace dg {
 
@@ -213,24 +214,6 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
     if (FACES) add_faces<N, 2>(m, T, e, t, o);
     lds_put<N, 2>(C, t1, t2, o);
   }
-}
-
-// The T^+ side of the lower face (D, 0) of element e on the thread's line
-// along D at (t1, t2), added to the element tile C: z l'(0) on the line, the
-// trace term on node 0 (the two scalars left in m.fb by the first pass).
-template <int N, int D, typename TC>
-__device__ __forceinline__ void lower_line(const MeshArgs<TC>& m, const Tables<TC>& T, int64_t e, int t1, int t2,
-                                           TC* C) {
-  constexpr int NN = N * N;
-  const TC* fb = m.fb + ((int64_t)e * 3 + D) * 2 * NN;
-  const int t = t1 + N * t2;
-  const TC out = fb[t], z = fb[NN + t];
-  TC yl[N];
-  lds_get<N, D>(C, t1, t2, yl);
-#pragma unroll
-  for (int i = 0; i < N; ++i) yl[i] += T.d0[i] * z;
-  yl[0] += out;
-  lds_put<N, D>(C, t1, t2, yl);
 }
 
 // Threads per block of the apply: 128 at n = 8, where the tiles of FP64 (13.8 KB
