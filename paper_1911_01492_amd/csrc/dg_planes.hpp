@@ -17,7 +17,7 @@
 // barrier.  (n = 3 leaves the fourth row idle; at n = 2 rows 2 and 3 hold a
 // second 4 x 4 block of elements, next in y.)  The lanes on the rim of the
 // 4 x 4 block load the plane of their neighbour outside it and reduce it
-// to the same face scalars.  A wave walks LZ layers upwards: the z-face data
+// to the same face scalars (dg_plane_lanes.hpp).  A wave walks LZ layers upwards: the z-face data
 // of the layer below stays in registers, and a layer is finished when the
 // next one's lower trace is known (below the first and above the last layer
 // only P2 is formed).
@@ -36,6 +36,7 @@
 #include "dg_internal.hpp"
 #include "dg_kernels.hpp"
 #include "dg_lines.hpp"
+#include "dg_plane_lanes.hpp"
 #include "dg_tables.hpp"
 
 namespace dg {
@@ -209,32 +210,13 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_planes(
   if (tile < ntx * nty * ntz) {
     int o[3];
     plane_tile(tile, ntx, nty, ntz, o);
-    const int row = lane >> 4, lx = lane & 3, ly = (lane >> 2) & 3;
+    const PlaneLane p = plane_lane<N>(m.nx, m.ny, m.periodic != 0, o[0], o[1], lane);
+    const int row = lane >> 4, z0 = o[2] * lz, z1 = min(z0 + lz, m.nz);
     const int r3 = N == 2 ? row & 1 : (N == 3 ? min(row, 2) : row);  // z of the lane's plane, y of its turned plane
-    // the last tile along an axis is moved back inside the mesh; the elements it
-    // then shares with the one before are stored by that one
-    const int ux = min(o[0] * 4, max(m.nx - 4, 0)) + lx;
-    const int uy = min(o[1] * BY, max(m.ny - BY, 0)) + ly + (N == 2 ? 4 * (row >> 1) : 0);
-    const int cx = min(ux, m.nx - 1), cy = min(uy, m.ny - 1);
-    const int z0 = o[2] * lz, z1 = min(z0 + lz, m.nz);
-    // An axis of one element with periodic wrap: all four lanes along it hold
-    // that element, and the shifts give an inner lane itself as both neighbours.
-    const bool selfX = m.nx == 1 && m.periodic, selfY = m.ny == 1 && m.periodic;
-    const bool act = (selfX ? lx == 1 : ux >= o[0] * 4 && ux < m.nx) &&
-                     (selfY ? uy == 1 : uy >= o[1] * BY && uy < m.ny) && (N != 3 || row < 3);
-    const bool hasXL = cx > 0 || m.periodic, hasXH = cx < m.nx - 1 || m.periodic;
-    const bool hasYL = cy > 0 || m.periodic, hasYH = cy < m.ny - 1 || m.periodic;
-    // The rim lanes: their low (first lane) or high neighbour (last lane, or the
-    // mesh's last element) is not beside them.  Each loads one plane per axis
-    // (both sides fall on one lane only where neither has a neighbour).
-    const bool rimXL = lx == 0, rimXH = !selfX && (lx == 3 || cx == m.nx - 1);
-    const bool rimYL = ly == 0, rimYH = !selfY && (ly == 3 || cy == m.ny - 1);
-    // element strides (in entries) to those neighbours, with the periodic wrap
-    const int64_t sx = N3, sy = (int64_t)m.nx * N3, sz = (int64_t)m.nx * m.ny * N3;
-    const int64_t dX = rimXL ? (cx > 0 ? -sx : (m.nx - 1) * sx) : (cx < m.nx - 1 ? sx : -(m.nx - 1) * sx);
-    const int64_t dY = rimYL ? (cy > 0 ? -sy : (m.ny - 1) * sy) : (cy < m.ny - 1 ? sy : -(m.ny - 1) * sy);
-    const bool okX = rimXL ? hasXL : rimXH && hasXH, okY = rimYL ? hasYL : rimYH && hasYH;
-    const int64_t e0 = cx + (int64_t)m.nx * cy, ez = (int64_t)m.nx * m.ny;
+    const bool act = p.act, hasXL = p.hasXL, hasXH = p.hasXH, hasYL = p.hasYL, hasYH = p.hasYH;
+    const bool rimXL = p.rimXL, rimXH = p.rimXH, rimYL = p.rimYL, rimYH = p.rimYH, okX = p.okX, okY = p.okY;
+    const int64_t sz = (int64_t)m.nx * m.ny * N3, dX = (int64_t)p.dX * N3, dY = (int64_t)p.dY * N3;
+    const int64_t e0 = p.cx + (int64_t)m.nx * p.cy, ez = (int64_t)m.nx * m.ny;
     const TIN* px = x + e0 * N3 + r3 * NN;  // the lane's plane in layer 0
 
     TC up[N], gp[N];  // z-face scalars (trace, derivative) of the layer below at its upper face

@@ -1,0 +1,131 @@
+"""The register-plane apply on meshes 2 to 9 elements wide along x or y and one
+to five layers high, against the oracle on sampled element rows: every place
+that the last element of a narrow axis can take in a 4 x 4 block of lanes.
+
+Tolerances: FP64 1e-12, FP32 / BF16 2e-5 (the bars of the other applies)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle import oracle as O  # noqa: E402
+from paper_1911_01492_amd import inputs as I  # noqa: E402
+from paper_1911_01492_amd.dg import DG_OK, DGOperator  # noqa: E402
+from tests.gpu_util import banner, bf16_dev, dev, host, rel_l2  # noqa: E402
+
+BCS = {"dirichlet": O.DIRICHLET, "periodic": O.PERIODIC}
+
+
+def _shape(axis, width, E):
+    a = int(np.ceil(np.sqrt(E / width)))
+    return (width, a, a + 1) if axis == "x" else (a, width, a + 1) if axis == "y" else (a, a + 1, width)
+
+
+def _rows(shape):
+    nx, ny, nz = shape
+    ends = [sorted({0, 1, 3, 4, 5, 8, d - 2, d - 1} & set(range(d))) for d in shape]
+    if ny > 16:
+        ends[1] = [0, ny - 1]
+    if nx > 16:
+        ends[0] = [0, nx - 1]
+    ends[2] = [0, min(3, nz - 1), nz - 1]
+    near = [x + nx * (y + ny * z) for x in ends[0] for y in ends[1] for z in ends[2]]
+    return np.unique(np.r_[near, I.fd_elements(nx * ny * nz, 16)])
+
+
+def _check(shape, bc, k, precs, transpose=False):
+    E = int(np.prod(shape))
+    theta, c = I.theta(E, seed=k), I.reaction(E)
+    m = O.Mesh(*shape, k, bc=BCS[bc], theta=theta, reaction=c)
+    op = DGOperator(*shape, k, bc, theta=dev(theta))
+    op.set_reaction(dev(c))
+    x = I.uniform_vector(m.ndof, seed=k)
+    el = _rows(shape)
+    for prec in precs:
+        banner(f"plane widths {shape} {bc} k={k} {prec}")
+        if prec == "bf16":
+            bits = I.to_bf16_bits(x)
+            X, xr = bf16_dev(bits), I.bf16_bits_to_f64(bits)
+        elif prec == "f32":
+            X, xr = dev(I.to_f32(x), torch.float32), I.to_f32(x).astype(np.float64)
+        else:
+            X, xr = dev(x), x
+        y = host(op.apply(X, prec=prec, transpose=transpose)).reshape(E, -1)[el]
+        err = rel_l2(y.ravel(), np.asarray(O.apply_rows(m, xr, el)).ravel())
+        assert err <= (1e-12 if prec == "f64" else 2e-5), (prec, err)
+
+
+# Element counts at which the kernel is used for all widths of the range (more
+# where its tiles' overhang along y makes it the slower one on small meshes).
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+@pytest.mark.parametrize("width", [2, 3, 4, 5, 6, 7, 8, 9])
+@pytest.mark.parametrize("axis", ["x", "y"])
+def test_q1(axis, width, bc):
+    _check(_shape(axis, width, 101000 if axis == "x" else 210000), bc, 1, ("f64", "f32", "bf16"))
+
+
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+@pytest.mark.parametrize("width", [2, 3, 4, 5, 6, 7, 8, 9])
+@pytest.mark.parametrize("axis", ["x", "y"])
+def test_q2(axis, width, bc):
+    _check(_shape(axis, width, 71000 if axis == "x" else 230000), bc, 2, ("f32", "bf16"))
+
+
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+@pytest.mark.parametrize("axis,width", [("x", 5), ("x", 7), ("y", 4), ("y", 8)])
+def test_q2_f64(axis, width, bc):
+    _check(_shape(axis, width, 402000), bc, 2, ("f64",))
+
+
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+@pytest.mark.parametrize("axis,width,E", [("x", w, 101000) for w in (2, 3, 4, 5, 6, 7, 9)] +
+                         [("y", 3, 101000), ("y", 4, 101000), ("y", 5, 600000), ("y", 6, 600000), ("y", 7, 101000),
+                          ("y", 8, 101000), ("y", 9, 330000)])
+def test_q3(axis, width, E, bc):
+    _check(_shape(axis, width, E), bc, 3, ("f32", "bf16"))
+
+
+@pytest.mark.parametrize("k,precs", [(1, ("f64", "f32", "bf16")), (2, ("f32", "bf16")), (3, ("f32", "bf16"))])
+@pytest.mark.parametrize("shape,bc", [((330, 320, 1), "periodic"), ((330, 320, 1), "dirichlet"), ((230, 230, 2), "periodic"),
+                                      ((150, 141, 5), "dirichlet"), ((2, 230, 230), "periodic"), ((1, 330, 320), "dirichlet")])
+def test_layers_and_single_elements(shape, bc, k, precs):
+    """Fewer layers than a wave walks (one layer being both of its neighbours), and one-element axes with both rims on one lane."""
+    _check(shape, bc, k, precs, transpose=True)
+
+
+def test_one_element_along_y_dirichlet():
+    _check((470, 1, 460), "dirichlet", 1, ("f64", "f32", "bf16"))
+    _check((480, 1, 480), "dirichlet", 2, ("f32", "bf16"))
+
+
+def test_f64_q2_periodic_and_its_solve():
+    """FP64 at n = 3, periodic with a reaction, and the <p, A p> of its CG: one
+    unpreconditioned step from x = 0 is (b.b / b.A b) b."""
+    shape = (75, 73, 74)
+    _check(shape, "periodic", 2, ("f64",), transpose=True)
+    banner(f"plane widths solve {shape}")
+    op = DGOperator(*shape, 2, "dirichlet", theta=dev(0.3 * I.theta(int(np.prod(shape)))))
+    b = dev(I.uniform_vector(op.ndof, seed=I.S_B))
+    x, _ = op.cg_solve(b, precond="none", maxit=1, rtol=1e-30)
+    z = torch.dot(b, b) / torch.dot(b, op.apply(b)) * b
+    assert float(torch.linalg.norm(x - z) / torch.linalg.norm(z)) <= 1e-12
+
+
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+def test_solve_five_wide(bc):
+    """A solve on a mesh five elements wide in y: its residual by the oracle's rows."""
+    shape = (205, 5, 205)
+    banner(f"plane widths solve {shape} {bc}")
+    E = int(np.prod(shape))
+    theta, c = 0.3 * I.theta(E), I.reaction(E)
+    m = O.Mesh(*shape, 1, bc=BCS[bc], theta=theta, reaction=c)
+    op = DGOperator(*shape, 1, bc, theta=dev(theta))
+    op.set_reaction(dev(c))
+    b = I.uniform_vector(m.ndof, seed=I.S_B)
+    x, info = op.cg_solve(dev(b), precond="block_jacobi", rtol=1e-8)
+    assert info["status"] == DG_OK
+    el = _rows(shape)
+    r = b.reshape(E, -1)[el].ravel() - np.asarray(O.apply_rows(m, host(x), el)).ravel()
+    assert np.linalg.norm(r) <= 1e-7 * np.linalg.norm(b)
