@@ -805,7 +805,7 @@ int64_t affine_tiles(int n, int nx, int ny, int nz) {
 }
 
 int64_t affine_partials(int n, int prec, int nx, int ny, int nz) {
-  return use_planes(n, prec, (int64_t)nx * ny * nz) ? plane_blocks(n, nx, ny, nz) : affine_tiles(n, nx, ny, nz);
+  return use_planes(n, prec, nx, ny, nz) ? plane_blocks(n, nx, ny, nz) : affine_tiles(n, nx, ny, nz);
 }
 
 template <int N, typename TIN, typename TOUT, typename TC, bool TRANS, bool DOT>
@@ -861,7 +861,7 @@ static hipError_t run_apply_n(int prec, int trans, int dot, const MeshArgs<doubl
 hipError_t launch_apply_affine(int n, int prec, int trans, int dot, const MeshArgs<double>& m64,
                                const MeshArgs<float>& m32, const void* x, void* y, double* partials,
                                CgState* st, int par, const int* skip, hipStream_t s) {
-  if (use_planes(n, prec, m64.E)) {  // the operator is symmetric: trans is the same product
+  if (use_planes(n, prec, m64.nx, m64.ny, m64.nz)) {  // the operator is symmetric: trans is the same product
     const hipError_t e = launch_apply_planes(n, prec, dot, m64, m32, x, y, partials, skip, s);
     if (e != hipSuccess || !dot || st == nullptr) return e;
     return launch_finish_dot(partials, plane_blocks(n, m64.nx, m64.ny, m64.nz), st, par, s);
@@ -937,7 +937,7 @@ static hipError_t run_multi_n(int prec, int trans, int nrhs, const MeshArgs<doub
 }
 hipError_t launch_apply_affine_multi(int n, int prec, int trans, int nrhs, const MeshArgs<double>& m64,
                                      const MeshArgs<float>& m32, const void* x, void* y, hipStream_t s) {
-  if (use_planes(n, prec, m64.E)) return launch_apply_planes(n, prec, 0, m64, m32, x, y, nullptr, nullptr, s, nrhs);
+  if (use_planes(n, prec, m64.nx, m64.ny, m64.nz)) return launch_apply_planes(n, prec, 0, m64, m32, x, y, nullptr, nullptr, s, nrhs);
   switch (n) {
     case 2: return run_multi_n<2>(prec, trans, nrhs, m64, m32, x, y, s);
     case 3: return run_multi_n<3>(prec, trans, nrhs, m64, m32, x, y, s);

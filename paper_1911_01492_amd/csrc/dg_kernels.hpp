@@ -50,7 +50,6 @@ hipError_t launch_apply_affine_mfma(int n, int dot, const MeshArgs<float>& m, co
 // the same with element planes in registers (dg_planes.hpp), for the meshes
 // that use_planes names: partials only (plane_blocks of them), nrhs vectors as
 // the second grid dimension
-bool use_planes(int n, int prec, int64_t E);
 int64_t plane_blocks(int n, int nx, int ny, int nz);
 hipError_t launch_apply_planes(int n, int prec, int dot, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
                                const void* x, void* y, double* partials, const int* skip, hipStream_t s, int nrhs = 1);

@@ -1,13 +1,50 @@
-// dg_plane_lanes.hpp -- which element a lane of k_apply_planes (dg_planes.hpp)
-// holds, whether it stores it, and where its x- and y-neighbours come from.
-// Plain integer logic, for the host too.
+// dg_plane_lanes.hpp -- which meshes k_apply_planes (dg_planes.hpp) is used
+// for, which element a lane of it holds, whether it stores it, and where its x-
+// and y-neighbours come from.  Plain integer logic, for the host too.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
+#include "dg_lines.hpp"
+
 namespace dg {
 
 __host__ __device__ constexpr int plane_by(int n) { return n == 2 ? 8 : 4; }  // elements of a wave's tile along y (4 along x)
+
+// Where that kernel is the faster one: large enough meshes, by type (the
+// crossings lie between these sizes, line kernel vs this, us): n = 2, 40^3 8.1
+// vs 7.9-8.2, 50^3 9.1-12.4 vs 7.9-10.2; n = 3, FP32 / BF16 33^3 9.3 vs 9.2-9.6,
+// 42^3 13-14 vs 12.4, FP64 53^3 33.3 vs 33.9, 97^3 211 vs 178; n = 4, FP32 31^3
+// 10.2 vs 10.8, 40^3 17.3 vs 16.2-17.8, 57^3 46 vs 42, BF16 31^3 9.5 vs 9.2,
+// 40^3 15.7 vs 13.6.
+// On meshes flat along y its tiles (8 elements along y at n = 2, 4 above) overhang
+// more than the line kernel's bricks (4, 3, 2). With q the elements of its tiles per
+// element of the bricks (up to 2), the crossing moves up by a power of q from where
+// q costs more than the kernel gains; this / line kernel in time on both sides: n =
+// 2 FP64 q = 1.33 106 x 9 x 106 0.88, q = 2 159 x 4 x 159 1.05, 236 x 4 x 236 0.98;
+// n = 3 FP32 q = 1.33 119 x 5 x 119 1.02, 225 x 5 x 225 0.88, BF16 159 x 6 x 159
+// 1.09, 259 x 6 x 259 0.89, FP64 q = 1.11 154 x 17 x 154 1.05, q = 1.14 184 x 21 x
+// 184 1.01-1.04, q = 1.33 343 x 6 x 343 1.19; n = 4 FP32 q = 1.2 106 x 9 x 106 1.11,
+// 184 x 9 x 184 0.99, q = 1.33 225 x 6 x 225 1.04, 317 x 6 x 317 0.93, q = 2 776 x 1
+// x 776 1.36, BF16 q = 1.2 86 x 9 x 86 1.07, 142 x 10 x 142 0.95, q = 1.33 184 x 6 x
+// 184 1.06, 317 x 6 x 317 0.91.
+inline bool use_planes(int n, int prec, int nx, int ny, int nz) {
+  struct Rule {
+    double from, q0;  // elements at q <= q0, times (q / q0)^power above
+    int power;
+  };
+  constexpr Rule rules[3][3] = {{{100000, 1.34, 2}, {100000, 1.34, 2}, {100000, 1.34, 2}},  // [n - 2][prec]
+                                {{400000, 1.07, 10}, {70000, 1.14, 7}, {70000, 1.14, 7}},
+                                {{1e300, 1.0, 0}, {100000, 1.05, 6}, {40000, 1.05, 8}}};
+  if (n < 2 || n > 4 || prec < 0 || prec > 2) return false;
+  const Rule& r = rules[n - 2][prec];
+  auto up = [](int a, int b) { return (double)((a + b - 1) / b) * b; };
+  const double q = up(ny, plane_by(n)) * nz / (up(ny, tile_y(n)) * up(nz, tile_z(n)));
+  double E = (double)nx * ny * nz;
+  if (q > r.q0)
+    for (int i = 0; i < r.power; ++i) E *= r.q0 / q;
+  return E >= r.from;
+}
 
 // A wave's tile is 4 elements along x and plane_by(n) along y, in 4 x 4 blocks
 // of lanes: lane = lx + 4 ly + 16 row, the rows being the element's planes

@@ -394,22 +394,6 @@ __global__ __launch_bounds__(kBlock, 2) void k_apply_planes(
 }
 
 // ---------------------------------------------------------------- launchers
-// Where this kernel is the faster one: large enough meshes, by type (the
-// crossings lie between these sizes, line kernel vs this, us): n = 2, 40^3 8.1
-// vs 7.9-8.2, 50^3 9.1-12.4 vs 7.9-10.2; n = 3, FP32 / BF16 33^3 9.3 vs 9.2-9.6,
-// 42^3 13-14 vs 12.4, FP64 53^3 33.3 vs 33.9, 97^3 211 vs 178; n = 4, FP32 31^3
-// 10.2 vs 10.8, 40^3 17.3 vs 16.2-17.8, 57^3 46 vs 42, BF16 31^3 9.5 vs 9.2,
-// 40^3 15.7 vs 13.6.
-bool use_planes(int n, int prec, int64_t E) {
-  if (prec < 0 || prec > 2) return false;
-  switch (n) {
-    case 2: return E >= 100000;
-    case 3: return E >= (prec == 0 ? 400000 : 70000);
-    case 4: return prec != 0 && E >= (prec == 1 ? 100000 : 40000);
-  }
-  return false;
-}
-
 // Layers per wave.  Each wave also forms P2 of the layers below and above its
 // own (about a third of a layer's work each), which favours many layers; but
 // fewer than about 3000 waves leave the 1024 SIMDs short of work: 63^3 Q1 FP64

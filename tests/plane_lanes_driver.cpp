@@ -59,7 +59,34 @@ static void mesh(int nx, int ny, bool periodic) {
     }
 }
 
+// the rule at ordinary meshes and at flat ones (the line kernel's bricks overhang less along y)
+static void rule(bool want, int n, int prec, int nx, int ny, int nz) {
+  if (use_planes(n, prec, nx, ny, nz) != want) {
+    ++fails;
+    std::printf("rule: n=%d prec=%d %dx%dx%d\n", n, prec, nx, ny, nz);
+  }
+}
+
 int main() {
+  for (int p = 0; p < 4; ++p) rule(p < 3, 2, p, 50, 50, 50);
+  for (int n = 5; n <= 8; ++n) rule(false, n, 1, 100, 100, 100);
+  rule(true, 2, 0, 160, 9, 160);
+  rule(true, 2, 0, 4, 200, 200);
+  rule(true, 2, 0, 200, 200, 3);
+  rule(false, 2, 0, 159, 4, 159);
+  rule(true, 2, 0, 448, 4, 448);
+  rule(true, 3, 0, 97, 97, 97);
+  rule(false, 3, 0, 343, 6, 343);
+  rule(true, 3, 1, 50, 50, 50);
+  rule(false, 3, 2, 159, 6, 159);
+  rule(true, 3, 2, 259, 6, 259);
+  rule(false, 4, 0, 100, 100, 100);
+  rule(true, 4, 1, 48, 48, 48);
+  rule(true, 4, 2, 36, 36, 36);
+  rule(false, 4, 1, 776, 1, 776);
+  rule(false, 4, 2, 225, 1, 225);
+  rule(false, 4, 1, 148, 6, 148);
+  rule(true, 4, 1, 317, 6, 317);
   for (int nx = 1; nx <= 17; ++nx)
     for (int ny = 1; ny <= 33; ++ny)
       for (int b = 0; b < 2; ++b) {

@@ -63,7 +63,7 @@ def _check(shape, bc, k, precs, transpose=False):
 @pytest.mark.parametrize("width", [2, 3, 4, 5, 6, 7, 8, 9])
 @pytest.mark.parametrize("axis", ["x", "y"])
 def test_q1(axis, width, bc):
-    _check(_shape(axis, width, 101000 if axis == "x" else 210000), bc, 1, ("f64", "f32", "bf16"))
+    _check(_shape(axis, width, 101000 if axis == "x" else 230000), bc, 1, ("f64", "f32", "bf16"))
 
 
 @pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
@@ -81,8 +81,8 @@ def test_q2_f64(axis, width, bc):
 
 @pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
 @pytest.mark.parametrize("axis,width,E", [("x", w, 101000) for w in (2, 3, 4, 5, 6, 7, 9)] +
-                         [("y", 3, 101000), ("y", 4, 101000), ("y", 5, 600000), ("y", 6, 600000), ("y", 7, 101000),
-                          ("y", 8, 101000), ("y", 9, 330000)])
+                         [("y", 3, 101000), ("y", 4, 101000), ("y", 5, 430000), ("y", 6, 430000), ("y", 7, 101000),
+                          ("y", 8, 101000), ("y", 9, 240000)])
 def test_q3(axis, width, E, bc):
     _check(_shape(axis, width, E), bc, 3, ("f32", "bf16"))
 
@@ -95,9 +95,10 @@ def test_layers_and_single_elements(shape, bc, k, precs):
     _check(shape, bc, k, precs, transpose=True)
 
 
-def test_one_element_along_y_dirichlet():
-    _check((470, 1, 460), "dirichlet", 1, ("f64", "f32", "bf16"))
-    _check((480, 1, 480), "dirichlet", 2, ("f32", "bf16"))
+@pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
+def test_one_element_along_y(bc):
+    _check((480, 1, 480), bc, 1, ("f64", "f32", "bf16"))
+    _check((480, 1, 480), bc, 2, ("f32", "bf16"))
 
 
 def test_f64_q2_periodic_and_its_solve():

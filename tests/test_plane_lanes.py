@@ -1,5 +1,6 @@
-"""The lane set-up of the register-plane apply over all small mesh widths, on
-the CPU: the header that the kernel uses, compiled for the host."""
+"""The lane set-up of the register-plane apply over all small mesh widths, and
+the rule that chooses it, on the CPU: the header that the library uses,
+compiled for the host."""
 import os
 import subprocess
 
@@ -10,7 +11,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
-def test_every_width(tmp_path):
+def test_every_width_and_the_rule(tmp_path):
     exe = str(tmp_path / "lanes")
     subprocess.run([HIPCC, "-x", "hip", "--cuda-host-only", "-O1", "-std=c++17",
                     "-I" + os.path.join(ROOT, "paper_1911_01492_amd", "csrc"),
