@@ -10,9 +10,11 @@
 
 namespace dg {
 
-// 1 / x and sqrt(x) of normal x from the hardware approximation by Newton's
-// method (quadratic, residuals by fused multiply-add), to within an ulp and
-// without the scaling steps of the full-range functions
+// 1 / x and sqrt(x) from the hardware approximation, to within an ulp and without
+// the scaling steps of the full-range functions: 1 / x by Newton's method, sqrt(x)
+// by Goldschmidt's iteration (residuals by fused multiply-add).  recip: x and 1 / x
+// normal (in FP32 a det J outside goes with areas whose squares FP32 cannot hold).
+// root: x zero or normal; in FP64 subnormal too (rsqf flushes them, rsq does not).
 __device__ __forceinline__ float recip(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(r, fmaf(-x, r, 1.0f), r);
@@ -23,11 +25,11 @@ __device__ __forceinline__ double recip(double x) {
   return fma(r, fma(-x, r, 1.0), r);
 }
 __device__ __forceinline__ float root(float x) {
-  const float y = __builtin_amdgcn_rsqf(x), g = x * y;
+  const float y = __builtin_amdgcn_rsqf(fmaxf(x, 0x1p-126f)), g = x * y;
   return fmaf(fmaf(-g, g, x), 0.5f * y, g);
 }
 __device__ __forceinline__ double root(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
+  const double y = __builtin_amdgcn_rsq(fmax(x, 0x1p-1022));
   double g = x * y, h = 0.5 * y;
   const double r = fma(-g, h, 0.5);
   g = fma(g, r, g);

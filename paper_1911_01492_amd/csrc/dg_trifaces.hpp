@@ -284,9 +284,12 @@ struct Corners {
 };
 
 // waves per SIMD asked of the register allocator: FP64 fits 128 registers up to
-// n = 5 (at n = 3 LDS leaves room for three) and 168 above
+// n = 5 (at n = 3 LDS leaves room for three) and 168 above; the sensitivity, which
+// reads a second vector, 128 up to n = 4 and, but for n = 5 and 8, two waves above.
+// FP32 takes 109 registers at n = 8 where it may, 85 with five waves (48^3 Q7 547 ->
+// 523 us).
 __host__ __device__ constexpr int face_min_waves(int n, int bytes, bool dA) {
-  if (bytes == 4) return 4;
+  if (bytes == 4) return n == 8 ? 5 : 4;
   return n <= (dA ? 4 : 5) && n != 3 ? 4 : (dA && (n == 6 || n == 7) ? 2 : 3);
 }
 
@@ -395,9 +398,10 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
     const TC odd = D == 1 ? TC(1) : TC(-1);
     const bool has = el[2 * f + 1] >= 0;
     const TC G = DA ? (has ? TC(0.5) : TC(1)) : m.G[(int64_t)6 * el[2 * f] + 2 * D + (lower ? 0 : 1)];
-    const TC pen = (D == 0 ? m.sg[0] : (D == 1 ? m.sg[1] : m.sg[2])) * G * (has ? TC(2) : TC(1));
+    TC pen = (D == 0 ? m.sg[0] : (D == 1 ? m.sg[1] : m.sg[2])) * G * (has ? TC(2) : TC(1));
     const TC gs = side != 0 || lower ? -G : G;  // sign of J on this side, outward N on a lower boundary
     const TC wj = T.gw[j];
+    TC scale = TC(1);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const TC tb = T.gx[i], w = wj * T.gw[i];
@@ -409,7 +413,19 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
       TC fl = (cd * gd[i] + ca * ga[i] + odd * (cb * gb[i])) * idet;
       fl += quad<0xB1>(fl);
       const TC Jm = v[i] - quad<0xB1>(v[i]);
-      const TC area = root(dot(Nv, Nv));
+      TC NN2 = dot(Nv, Nv);
+      if constexpr (sizeof(TC) == 4) {
+        // in FP32 |N|^2 is subnormal at edges near 1e-10, where |N| is not: with the first
+        // point's below 2^-62 the line's are scaled by 2^64 (N is affine in xi_B, and the
+        // Gauss points are off the ends: they differ by less than 2^12 on a valid face)
+        if (i == 0) {
+          const bool tiny = NN2 < TC(0x1p-62);
+          scale = tiny ? TC(0x1p64) : TC(1);
+          pen *= tiny ? TC(0x1p-32) : TC(1);
+        }
+        NN2 *= scale;
+      }
+      const TC area = root(NN2);
       const TC co = -w * gs * Jm * idet;
       v[i] = w * (pen * area * Jm - gs * fl);
       gd[i] = co * cd;
