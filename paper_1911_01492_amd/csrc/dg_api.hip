@@ -308,8 +308,6 @@ bool build_tables(int n, Tables<double>& T) {
       Mv[i * n + j] = m;
       Sv[i * n + j] = s;
       Cv[i * n + j] = cm;
-      T.B[i * kMaxN + j] = B[i * n + j];
-      T.D[i * kMaxN + j] = D[i * n + j];
       T.BB[i * kMaxN + j] = B[i * n + j] * B[i * n + j];
       T.BD[i * kMaxN + j] = B[i * n + j] * D[i * n + j];
       T.DD[i * kMaxN + j] = D[i * n + j] * D[i * n + j];
@@ -350,12 +348,7 @@ void tables_to_f32(const Tables<double>& a, Tables<float>& b) {
     b.M[i] = (float)a.M[i];
     b.Mis[i] = (float)a.Mis[i];
     b.S[i] = (float)a.S[i];
-    b.B[i] = (float)a.B[i];
-    b.D[i] = (float)a.D[i];
     b.Cd[i] = (float)a.Cd[i];
-    b.BB[i] = (float)a.BB[i];
-    b.BD[i] = (float)a.BD[i];
-    b.DD[i] = (float)a.DD[i];
   }
   for (int i = 0; i < kMaxN; ++i) {
     b.d0[i] = (float)a.d0[i];

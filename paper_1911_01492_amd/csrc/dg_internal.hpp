@@ -31,27 +31,32 @@ struct EvenOdd {
   T mm;
 };
 
+// products of basis values and derivatives at the Gauss points, B_qi B_qi, B_qi D_qi,
+// D_qi D_qi (B_qi = l_i(x_q), D_qi = l_i'(x_q)): the diagonal a(phi_i, phi_i) by sum
+// factorisation on trilinear meshes, FP64 only
 template <typename T>
-struct Tables {
+struct DiagTables {};
+template <>
+struct DiagTables<double> {
+  double BB[kMaxN * kMaxN], BD[kMaxN * kMaxN], DD[kMaxN * kMaxN];
+};
+
+template <typename T>
+struct Tables : DiagTables<T> {
   T M[kMaxN * kMaxN];   // mass       M_ij = sum_q w_q l_i(x_q) l_j(x_q)
   T S[kMaxN * kMaxN];   // stiffness  S_ij = sum_q w_q l_i'(x_q) l_j'(x_q)
-  T B[kMaxN * kMaxN];   // interpolation GLL -> Gauss, B_qi = l_i(x_q)
-  T D[kMaxN * kMaxN];   // derivative at the Gauss points, D_qi = l_i'(x_q)
   T d0[kMaxN];          // l_i'(0)
   T d1[kMaxN];          // l_i'(1)
   T gw[kMaxN];          // Gauss weights on [0,1]
   T gx[kMaxN];          // Gauss points on [0,1]
   EvenOdd<T> eM, eS;    // M and S (symmetric, centro-symmetric)
-  EvenOdd<T> eB, eBt;   // B and B^T (centro-symmetric)
+  EvenOdd<T> eB, eBt;   // interpolation GLL -> Gauss, B_qi = l_i(x_q), and B^T (centro-symmetric)
   EvenOdd<T> eDg, eDgt; // Dg and Dg^T, Dg the collocation derivative on the Gauss
-                        // points (Dg B = D; centro-antisymmetric)
+                        // points (Dg B = D, D_qi = l_i'(x_q); centro-antisymmetric)
   T Mis[kMaxN * kMaxN]; // M^{-1/2} (symmetric), for the generalized eigenproblems of
                         // the element block-Jacobi preconditioner
   T Cd[kMaxN * kMaxN];  // mixed matrix C_ij = sum_q w_q l_i(x_q) l_j'(x_q) = int l_i l_j'
   EvenOdd<T> eC;        // C by its even-odd halves (centro-antisymmetric)
-  T BB[kMaxN * kMaxN];  // products of basis values and derivatives at the Gauss points,
-  T BD[kMaxN * kMaxN];  // B_qi B_qi, B_qi D_qi, D_qi D_qi: the diagonal a(phi_i, phi_i) by
-  T DD[kMaxN * kMaxN];  // sum factorisation (trilinear meshes)
 };
 
 // Eigen-decomposition of a symmetric n x n matrix (row stride kMaxN) by the

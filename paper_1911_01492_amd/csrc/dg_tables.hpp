@@ -14,8 +14,8 @@ namespace dg {
 
 template <typename T>
 struct KTables {
-  T M[kMaxN * kMaxN], S[kMaxN * kMaxN], B[kMaxN * kMaxN], D[kMaxN * kMaxN], Cd[kMaxN * kMaxN];
-  T d0[kMaxN], d1[kMaxN], gw[kMaxN], gx[kMaxN];
+  T M[kMaxN * kMaxN], S[kMaxN * kMaxN];
+  T d0[kMaxN], d1[kMaxN];
   EvenOdd<T> eM, eS, eB, eBt, eDg, eDgt, eC;
 };
 
@@ -169,18 +169,12 @@ constexpr KTables<T> make() {
   Bt = centro(N, Bt, 1.0, false);
   Dg = centro(N, Dg, -1.0, false);
   Dgt = centro(N, Dgt, -1.0, false);
-  D = centro(N, D, -1.0, false);
   C = centro(N, C, -1.0, false);
   store(N, M, t.M);
   store(N, S, t.S);
-  store(N, B, t.B);
-  store(N, D, t.D);
-  store(N, C, t.Cd);
   for (int i = 0; i < N; ++i) {
     t.d0[i] = (T)lagrange_d(N, l.x, i, 0.0);
     t.d1[N - 1 - i] = -t.d0[i];
-    t.gw[i] = (T)g.w[i];
-    t.gx[i] = (T)g.x[i];
   }
   even_odd(N, M, t.eM);
   even_odd(N, S, t.eS);
