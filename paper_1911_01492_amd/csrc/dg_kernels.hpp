@@ -47,12 +47,6 @@ hipError_t launch_apply_affine(int n, int prec, int trans, int dot, const MeshAr
 bool mfma_apply_supported(int n);
 hipError_t launch_apply_affine_mfma(int n, int dot, const MeshArgs<float>& m, const uint16_t* x, float* y,
                                     double* partials, const int* skip, hipStream_t s, int nrhs = 1);
-// the same with element planes in registers (dg_planes.hpp), for the meshes
-// that use_planes names: partials only (plane_blocks of them), nrhs vectors as
-// the second grid dimension
-int64_t plane_blocks(int n, int nx, int ny, int nz);
-hipError_t launch_apply_planes(int n, int prec, int dot, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
-                               const void* x, void* y, double* partials, const int* skip, hipStream_t s, int nrhs = 1);
 // Y = A X for nrhs vectors stored one after another (affine meshes, no fused
 // dot): the vectors are the second grid dimension of the apply kernels
 hipError_t launch_apply_affine_multi(int n, int prec, int trans, int nrhs, const MeshArgs<double>& m64,
@@ -105,10 +99,6 @@ hipError_t launch_dA_affine(int n, const MeshArgs<double>& m, const double* u, c
 
 // trilinear meshes
 int64_t tri_apply_blocks(int n, int64_t E);  // blocks (and block partials) of the apply
-hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const MeshArgs<float>& m32, const void* x,
-                            const int* skip, hipStream_t s);
-hipError_t launch_tri_faces_dA(int n, const MeshArgs<double>& m, const double* u, const double* v, double* parts,
-                               hipStream_t s);
 hipError_t launch_apply_trilinear(int n, int prec, int trans, int dot, const MeshArgs<double>& m64,
                                   const MeshArgs<float>& m32, const void* x, void* y, double* partials,
                                   CgState* st, int par, const int* skip, hipStream_t s);

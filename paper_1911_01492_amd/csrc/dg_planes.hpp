@@ -409,7 +409,8 @@ static int plane_layers(int n, int nx, int ny, int nz) {
   while (lz > 1 && cols * ((nz + lz - 1) / lz) < 3000) lz >>= 1;
   return lz < nz ? lz : nz;
 }
-int64_t plane_blocks(int n, int nx, int ny, int nz) {
+// blocks (and block partials) of the kernel
+static int64_t plane_blocks(int n, int nx, int ny, int nz) {
   const int lz = plane_layers(n, nx, ny, nz);
   const int64_t t = (int64_t)((nx + 3) / 4) * ((ny + plane_by(n) - 1) / plane_by(n)) * ((nz + lz - 1) / lz);
   return (t + kBlock / 64 - 1) / (kBlock / 64);
@@ -440,8 +441,11 @@ static hipError_t run_planes_prec(int prec, int dot, const MeshArgs<double>& m64
   }
   return hipErrorInvalidValue;
 }
-hipError_t launch_apply_planes(int n, int prec, int dot, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
-                               const void* x, void* y, double* partials, const int* skip, hipStream_t s, int nrhs) {
+// y = A x as launch_apply_affine, for the meshes that use_planes names: partials
+// only, nrhs vectors as the second grid dimension
+static hipError_t launch_apply_planes(int n, int prec, int dot, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
+                                      const void* x, void* y, double* partials, const int* skip, hipStream_t s,
+                                      int nrhs = 1) {
   switch (n) {
     case 2: return run_planes_prec<2>(prec, dot, m64, m32, x, y, partials, skip, s, nrhs);
     case 3: return run_planes_prec<3>(prec, dot, m64, m32, x, y, partials, skip, s, nrhs);

@@ -557,8 +557,8 @@ static hipError_t run_tri_faces_dA(const MeshArgs<double>& m, const double* u, c
                      parts);
   return hipGetLastError();
 }
-hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const MeshArgs<float>& m32, const void* x,
-                            const int* skip, hipStream_t s) {
+static hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const MeshArgs<float>& m32,
+                                   const void* x, const int* skip, hipStream_t s) {
   switch (n) {
     case 2: return run_tri_faces<2>(prec, m64, m32, x, skip, s);
     case 3: return run_tri_faces<3>(prec, m64, m32, x, skip, s);
@@ -570,8 +570,8 @@ hipError_t launch_tri_faces(int n, int prec, const MeshArgs<double>& m64, const 
   }
   return hipErrorInvalidValue;
 }
-hipError_t launch_tri_faces_dA(int n, const MeshArgs<double>& m, const double* u, const double* v, double* parts,
-                               hipStream_t s) {
+static hipError_t launch_tri_faces_dA(int n, const MeshArgs<double>& m, const double* u, const double* v,
+                                      double* parts, hipStream_t s) {
   switch (n) {
     case 2: return run_tri_faces_dA<2>(m, u, v, parts, s);
     case 3: return run_tri_faces_dA<3>(m, u, v, parts, s);
