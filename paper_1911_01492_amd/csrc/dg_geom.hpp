@@ -12,9 +12,9 @@ namespace dg {
 
 // 1 / x and sqrt(x) from the hardware approximation, to within an ulp and without
 // the scaling steps of the full-range functions: 1 / x by Newton's method, sqrt(x)
-// by Goldschmidt's iteration (residuals by fused multiply-add).  recip: x and 1 / x
-// normal (in FP32 a det J outside goes with areas whose squares FP32 cannot hold).
-// root: x zero or normal; in FP64 subnormal too (rsqf flushes them, rsq does not).
+// by Goldschmidt's iteration (residuals by fused multiply-add).
+// recip: x and 1 / x normal.  root: x zero or normal; in FP64 subnormal too (rsqf
+// flushes them, rsq does not).
 __device__ __forceinline__ float recip(float x) {
   const float r = __builtin_amdgcn_rcpf(x);
   return fmaf(r, fmaf(-x, r, 1.0f), r);
@@ -24,6 +24,11 @@ __device__ __forceinline__ double recip(double x) {
   r = fma(r, fma(-x, r, 1.0), r);
   return fma(r, fma(-x, r, 1.0), r);
 }
+// 1 / det J of a trilinear element: in FP32 through 2^24 det, which is normal
+// wherever 1 / det is finite, and finite wherever the squares of the areas are
+// (det^2 is about the product of the areas, so det < 2^96)
+__device__ __forceinline__ float recip_det(float x) { return 0x1p24f * recip(0x1p24f * x); }
+__device__ __forceinline__ double recip_det(double x) { return recip(x); }
 __device__ __forceinline__ float root(float x) {
   const float y = __builtin_amdgcn_rsqf(fmaxf(x, 0x1p-126f)), g = x * y;
   return fmaf(fmaf(-g, g, x), 0.5f * y, g);

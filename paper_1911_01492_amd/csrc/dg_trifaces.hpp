@@ -401,30 +401,34 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
     TC pen = (D == 0 ? m.sg[0] : (D == 1 ? m.sg[1] : m.sg[2])) * G * (has ? TC(2) : TC(1));
     const TC gs = side != 0 || lower ? -G : G;  // sign of J on this side, outward N on a lower boundary
     const TC wj = T.gw[j];
-    TC scale = TC(1);
+    [[maybe_unused]] TC sN = TC(1);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       const TC tb = T.gx[i], w = wj * T.gw[i];
       const V3<TC> ja = lin(L.ap, tb, L.aq), jd = lin(L.dp, tb, L.dq);
       const V3<TC> nd = cross(ja, L.jb);
       const V3<TC> Nv = {quad<0xA0>(nd.x), quad<0xA0>(nd.y), quad<0xA0>(nd.z)};
-      const TC idet = recip(dot(jd, nd));
-      const TC cd = dot(nd, Nv), ca = dot(cross(L.jb, jd), Nv), cb = dot(cross(jd, ja), Nv);
+      // c = adj N / det; in FP32 N is divided first: nothing of h^4 but |N|^2 is formed,
+      TC idet = recip_det(dot(jd, nd)), NN2 = dot(Nv, Nv);
+      V3<TC> Nc = Nv;
+      if constexpr (sizeof(TC) == 4) {
+        Nc = {Nv.x * idet, Nv.y * idet, Nv.z * idet};
+        idet = TC(1);
+        // which is subnormal at edges near 1e-10, where |N| is not: where it is below 2^-62
+        // at the line's first point, 2^64 |N|^2 and 2^-32 of the penalty instead (N is affine
+        // in xi_B and the Gauss points are off the ends, so on a valid face |N|^2 differs by
+        // less than 2^12 along the line)
+        if (i == 0) {
+          const bool tiny = NN2 < 0x1p-62f;
+          sN = tiny ? 0x1p64f : 1.0f;
+          pen *= tiny ? 0x1p-32f : 1.0f;
+        }
+        NN2 *= sN;
+      }
+      const TC cd = dot(nd, Nc), ca = dot(cross(L.jb, jd), Nc), cb = dot(cross(jd, ja), Nc);
       TC fl = (cd * gd[i] + ca * ga[i] + odd * (cb * gb[i])) * idet;
       fl += quad<0xB1>(fl);
       const TC Jm = v[i] - quad<0xB1>(v[i]);
-      TC NN2 = dot(Nv, Nv);
-      if constexpr (sizeof(TC) == 4) {
-        // in FP32 |N|^2 is subnormal at edges near 1e-10, where |N| is not: with the first
-        // point's below 2^-62 the line's are scaled by 2^64 (N is affine in xi_B, and the
-        // Gauss points are off the ends: they differ by less than 2^12 on a valid face)
-        if (i == 0) {
-          const bool tiny = NN2 < TC(0x1p-62);
-          scale = tiny ? TC(0x1p64) : TC(1);
-          pen *= tiny ? TC(0x1p-32) : TC(1);
-        }
-        NN2 *= scale;
-      }
       const TC area = root(NN2);
       const TC co = -w * gs * Jm * idet;
       v[i] = w * (pen * area * Jm - gs * fl);

@@ -146,7 +146,7 @@ __device__ void tri_volume(const MeshArgs<TC>& m, const Tables<TC>& T, const TIN
         adj3(J, Aj);
         // det J from the adjugate's first row
         const TC dJ = fabs(J[0][0] * Aj[0][0] + J[1][0] * Aj[0][1] + J[2][0] * Aj[0][2]);
-        const TC c = wq12 * T.gw[q] * recip(dJ);
+        const TC c = wq12 * T.gw[q] * recip_det(dJ);
         v[q] *= cw12 * T.gw[q] * dJ;  // reaction c w |det J| u at the point
         if constexpr (N <= 5 && sizeof(TC) == 8) {
           // G gr with G formed: more operations, but at most 128 registers (four waves per SIMD)

@@ -1,10 +1,10 @@
 """Trilinear applies on meshes far from unit size.  The 1D scalings come from the
 element counts, so with the vertices scaled by s the volume and consistency
 terms scale by s and the penalty by s^2; the squares of the face areas go like
-s^4 and are subnormal in FP32 at edges near 1e-10, where the area itself is not.
+s^4, are subnormal in FP32 at edges near 1e-10, zero at 1e-12 (where the penalty
+is 1e-10 of the rest) and near the largest number at 3e9.
 
-Tolerances: FP64 1e-12; FP32 / BF16 2e-5 (the bars of the other applies) where
-|N|^2 has at least 17 bits, h^4 >= 2e-40."""
+Tolerances: FP64 1e-12; FP32 / BF16 2e-5 (the bars of the other applies)."""
 import numpy as np
 import pytest
 
@@ -19,7 +19,7 @@ from tests.gpu_util import banner, bf16_dev, dev, host, rel_l2  # noqa: E402
 from tests.test_gpu_trilinear import BCS, box_vertices  # noqa: E402
 
 
-@pytest.mark.parametrize("scale", [1e5, 1e-5, 1.5e-9, 6e-10])
+@pytest.mark.parametrize("scale", [8e9, 1e5, 1e-5, 1.5e-9, 6e-10, 1e-10, 4e-12])
 @pytest.mark.parametrize("k", [1, 2, 4, 7])
 @pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
 def test_scaled_vertices(bc, k, scale):
@@ -37,6 +37,19 @@ def test_scaled_vertices(bc, k, scale):
                              ("f32", dev(I.to_f32(x), torch.float32), I.to_f32(x).astype(np.float64), 2e-5),
                              ("bf16", bf16_dev(bits), I.bf16_bits_to_f64(bits), 2e-5)):
         assert rel_l2(host(op.apply(X, prec=prec)), A @ xr) <= tol, prec
+
+
+@pytest.mark.parametrize("k", [1, 3, 6])
+def test_subnormal_determinants(k):
+    """Elements 3e-11 x 3e-11 x 5e-17: det J straddles FP32's smallest normal number."""
+    shape = (4, 3, 2)
+    banner(f"trilinear subnormal det k={k}")
+    V = 1e-10 * box_vertices(*shape, seed=k) * np.array([1.0, 1.0, 1e-6])
+    m = O.Mesh(*shape, k, vertices=V)
+    op = DGOperator(*shape, k, "dirichlet", vertices=dev(V))
+    x32 = I.to_f32(I.uniform_vector(m.ndof, seed=k))
+    y = op.apply(dev(x32, torch.float32), prec="f32")
+    assert rel_l2(host(y), O.assemble(m) @ x32.astype(np.float64)) <= 2e-5
 
 
 @pytest.mark.parametrize("prec,dtype,scale", [("f32", torch.float32, 1e-11), ("f64", torch.float64, 1e-80)])
