@@ -140,8 +140,9 @@ int dg_apply(dg_ctx* ctx, int prec, const void* x, void* y, void* stream);
  * consistency and symmetry terms are mirror images and the penalty term is
  * symmetric), so A^T = A.  Affine meshes: evaluated from the transposed 1D
  * operators and the transposed face algebra (equal to A x up to rounding);
- * parallelepiped and trilinear meshes: the apply itself.  Arguments and errors
- * as dg_apply. */
+ * large affine meshes at k <= 3 (those of the register-plane kernel: from 40000
+ * to 400000 elements on, by degree and precision), parallelepiped and trilinear
+ * meshes: the apply itself, bit for bit.  Arguments and errors as dg_apply. */
 int dg_apply_transpose(dg_ctx* ctx, int prec, const void* x, void* y, void* stream);
 
 /* Y = A X (transpose = 1: A^T X) for nrhs vectors at once, the multiple

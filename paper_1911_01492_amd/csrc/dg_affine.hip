@@ -146,7 +146,7 @@ __global__ __launch_bounds__(apply_block(N), (N == 5 && sizeof(TC) == 8) ? 8 : 1
   // FP32 at n = 3..7: x is loaded once, as z-lines (whose lanes are adjacent in
   // memory), into a tile of its own that all three orientations read, instead
   // of three times with the lanes of the x- and y-lines n and n^2 values apart
-  // (at n = 5 in FP64 the texture path is busy 96% of the time with these).
+  // (at n = 5 in FP64 the address unit is busy 96% of the time with these).
   // 58^3 Q4 FP32 98 -> 88 us, BF16 86 -> 79, 42^3 Q6 FP32 108 -> 99.  In FP64
   // the tile's LDS traffic costs more than it saves (73^3 Q3 152 -> 168 us),
   // and so does its space at n = 8 in FP32 (37^3 Q7 79 -> 90).

@@ -25,11 +25,11 @@
 // Against the line kernel this takes 30-40% fewer VALU instructions per DOF, no
 // LDS traffic and a third of the cache accesses; at two to four waves per SIMD
 // (110 VGPRs at n = 2 in FP64, 136 at n = 4 in FP32) it is bound by its own
-// instruction stream and load latency.  Line kernel -> this, us: 146^3 Q1 FP64
-// 215 -> 156, FP32 140 -> 90, BF16 122 -> 55; 97^3 Q2 FP64 211 -> 178, FP32
-// 135 -> 83, BF16 116 -> 73; 73^3 Q3 FP32 89 -> 75, BF16 77 -> 57.  In FP64 at
-// n = 4 the planes take all 256 VGPRs and it ties with the line kernel (149 vs
-// 152), so it is not built there.
+// instruction stream and load latency (79^3 Q1 FP64: VALU busy 48%, address unit 63%,
+// waiting 53%).  Line kernel before it -> this, us: 146^3 Q1 FP64 198 -> 148, FP32
+// 119 -> 61, BF16 128 -> 50; 97^3 Q2 FP64 160 -> 148, FP32 123 -> 71, BF16 134 -> 73;
+// 73^3 Q3 FP32 79 -> 63, BF16 83 -> 55.  In FP64 at n = 4 the planes take all 256 VGPRs
+// and it ties with the line kernel (149 vs 152), so it is not built there.
 // Part of the translation unit dg_affine.hip.
 #pragma once
 

@@ -24,14 +24,15 @@
 //
 // With one thread per face point instead (each output a dot product of n LDS
 // values with a table row of the thread's own, in one kernel with the volume
-// part) an apply of 48^3 Q7 took 1500 us; with this kernel 960 us (faces 460,
-// volume 495), against 450 us for its arithmetic (581 flop per DOF) at the rate of a
-// large FP64 product; the two kernels move 3.2 GB.
-// FP64 arithmetic bounds it: at n = 8 1900 vector instructions per wave, 57 % of
-// the cycles at three waves per SIMD (about 100 of them per face point for the
-// two conormals, 1 / det, |N| and the exchange); the address unit is busy 45 %.
-// Others, apply before -> now: 73^3 Q3 823 -> 688 us, 58^3 Q4 862 -> 663, 42^3 Q6
-// 797 -> 617, 146^3 Q1 2022 -> 1486; FP32 37^3 Q7 322 -> 244.
+// part) an apply of 48^3 Q7 took 1500 us; with this kernel 945 us back to back (1090
+// in a run of a few applies: faces 516, volume 587), against 450 us for its
+// arithmetic (581 flop per DOF) at the rate of a large FP64 product; the two kernels
+// move 3.2 GB.  FP64 arithmetic bounds it: at n = 8 1764 vector instructions per wave,
+// 65% of the cycles at three waves per SIMD (about 100 of them per face point for
+// the two conormals, 1 / det, |N| and the exchange); the address unit is busy 59%.
+// In FP32 (1647 instructions) the VALU is saturated.
+// Others, apply before -> now: 73^3 Q3 919 -> 612 us, 58^3 Q4 899 -> 568, 42^3 Q6
+// 873 -> 537, 146^3 Q1 2076 -> 1412; FP32 37^3 Q7 339 -> 229, 48^3 Q7 713 -> 515.
 // Part of the translation unit dg_trilinear.hip.
 #pragma once
 
@@ -435,8 +436,8 @@ __global__ __launch_bounds__(kFaceBlock) __attribute__((amdgpu_waves_per_eu(face
       gd[i] = co * cd;
       ga[i] = co * ca;
       gb[i] = co * cb;
-      // points in groups: no spills at 168 (n = 8) and 128 (n = 5) registers (one by
-      // one the faces of 48^3 Q7 took 497 us, by four 450)
+      // points in groups: no spills at 168 (n = 8) and 128 (n = 5) registers (back to back
+      // the faces of 48^3 Q7 took 497 us one by one, 450 by four)
       if (sizeof(TC) == 8 && ((N == 8 && i == 3) || (N == 5 && (i & 1)))) __builtin_amdgcn_sched_barrier(0);
     }
   }

@@ -228,9 +228,9 @@ __host__ __device__ constexpr int tri_min_waves(int n, int bytes) {
 }
 
 // Volume part of the apply and the face rows of k_tri_faces.  DOT: block
-// partials of <x, y> for the CG.  48^3 Q7 in FP64: 495 us, 1.6 GB (3.2 TB/s), 62 %
-// of the cycles issue vector instructions (blocks of 256: 557 us; with the
-// gradient's metric formed at every point and IEEE division 532 us).
+// partials of <x, y> for the CG.  48^3 Q7 in FP64, back to back: 495 us, 1.6 GB
+// (3.2 TB/s), 63% of the cycles issue vector instructions (blocks of 256: 557 us; with
+// the gradient's metric formed at every point and IEEE division 532 us).
 template <int N, typename TIN, typename TOUT, typename TC, bool AFF, bool DOT>
 __global__ __launch_bounds__(tri_block(N)) __attribute__((amdgpu_waves_per_eu(tri_min_waves(N, sizeof(TC))))) void k_apply_trilinear(
     MeshArgs<TC> m, const TIN* __restrict__ x, TOUT* __restrict__ y, double* partials, const int* skip) {
