@@ -74,7 +74,7 @@ def test_q2(axis, width, bc):
 
 
 @pytest.mark.parametrize("bc", ["dirichlet", "periodic"])
-@pytest.mark.parametrize("axis,width", [("x", 5), ("x", 7), ("y", 4), ("y", 8)])
+@pytest.mark.parametrize("axis,width", [("x", w) for w in (2, 3, 4, 5, 6, 7, 8, 9)] + [("y", 4), ("y", 7), ("y", 8), ("y", 11)])
 def test_q2_f64(axis, width, bc):
     _check(_shape(axis, width, 402000), bc, 2, ("f64",))
 
