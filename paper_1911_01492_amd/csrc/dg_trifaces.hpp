@@ -287,8 +287,8 @@ struct Corners {
 // waves per SIMD asked of the register allocator: FP64 fits 128 registers up to
 // n = 5 (at n = 3 LDS leaves room for three) and 168 above; the sensitivity, which
 // reads a second vector, 128 up to n = 4 and, but for n = 5 and 8, two waves above.
-// FP32 takes 109 registers at n = 8 where it may, 85 with five waves (48^3 Q7 547 ->
-// 523 us).
+// FP32 takes 104 registers at n = 8 where it may, 89 with five waves (48^3 Q7 531 ->
+// 519 us; six spill, 543).
 __host__ __device__ constexpr int face_min_waves(int n, int bytes, bool dA) {
   if (bytes == 4) return n == 8 ? 5 : 4;
   return n <= (dA ? 4 : 5) && n != 3 ? 4 : (dA && (n == 6 || n == 7) ? 2 : 3);
